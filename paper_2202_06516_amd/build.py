@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "_lib", "liblbm.so")
 
-SOURCES = ["api.hip", "host.cpp", "batch.hip", "unet.hip"]
+SOURCES = ["api.hip", "host.cpp", "batch.hip", "step2d.hip", "unet.hip"]
 
 # Packed FP32 instructions stay off: plain float code only.
 HIP_FLAGS = [

@@ -14,6 +14,7 @@
 #include "kernels.hpp"
 #include "fused.hpp"
 #include "phasefield.hpp"
+#include "step2d.hpp"
 #include "young.hpp"
 
 using namespace lbm;
@@ -121,6 +122,12 @@ struct lbm_ctx {
     lbm_measure_opts mopts{0, 32, 0.0};
     long long t = 0;  // host mirror of the step counter
     hipGraphExec_t graph[2] = {nullptr, nullptr};
+    // the single-launch step of D2Q9 lattices (step2d.hpp): its tiles and
+    // shape, and its captured windows without / with the body force
+    bool one2d = false;
+    hipGraphExec_t graph2d[2] = {nullptr, nullptr};
+    Tile2d* tiles = nullptr;
+    int ntiles = 0, shape2d = 0;
     // phase-field model: the order-parameter populations (same form and
     // buffer parity as f) and the order parameter, whose solid layers hold phi_w
     bool pf = false;
@@ -132,6 +139,11 @@ namespace {
 
 // the field whose isolevel is the interface: phi in the phase-field model, else rho
 inline void* mfield(const lbm_ctx* c) { return c->pf ? c->phi : c->rho; }
+
+// the model of the single-launch D2Q9 step
+int model2d(const lbm_ctx* c) {
+    return c->pf ? M2_PHASE : (c->cfg.model == LBM_MODEL_PSEUDOPOTENTIAL ? M2_PSEUDO : M2_CHEM);
+}
 
 lbm_status fail(lbm_ctx* c, lbm_status s, const std::string& msg) {
     if (c) c->err = msg;
@@ -162,10 +174,10 @@ lbm_status dalloc(lbm_ctx* c, T** p, size_t bytes) {
 }
 
 void drop_graphs(lbm_ctx* c) {
-    for (auto& g : c->graph)
-        if (g) {
-            (void)hipGraphExecDestroy(g);
-            g = nullptr;
+    for (hipGraphExec_t* g : {&c->graph[0], &c->graph[1], &c->graph2d[0], &c->graph2d[1]})
+        if (*g) {
+            (void)hipGraphExecDestroy(*g);
+            *g = nullptr;
         }
 }
 
@@ -391,6 +403,50 @@ struct Run {
         k_finalize<L, R><<<1, 64, 0, c->stream>>>(rho, c->ctl, c->d, mp, c->series, c->last, 1, ys, c->yseries);
         mark(6);
         if (kinds) kinds[k] = -1;
+    }
+
+    // One step in a single launch (D2Q9, pull form) from f[src] into f[1-src].
+    // meas: a measure step, followed by the crossing search and the finalize,
+    // which counts the step; otherwise the launch itself counts it.
+    static void one2d_launches(lbm_ctx* c, int src, const MeasureParams& mp, bool meas, bool grav) {
+        if constexpr (L::D == 2) {
+            Step2dArgs a{};
+            a.precision = c->cfg.precision;
+            a.model = model2d(c);
+            a.mrt = c->cfg.collision == LBM_MRT;
+            a.shape = c->shape2d;
+            a.tiles = c->tiles;
+            a.ntiles = c->ntiles;
+            a.N = c->d.N;
+            a.fin = c->f[src];
+            a.fout = c->f[1 - src];
+            a.gin = c->g[src];
+            a.gout = c->g[1 - src];
+            a.field = mfield(c);
+            a.wall = c->pf ? c->phi : c->mu;
+            a.cls = c->cls;
+            a.bc = wall(c);
+            a.ctl = c->ctl;
+            a.slots = &c->ctl->m;
+            a.rho_m = mp.rho_m;
+            a.inv_b = 1.0 / c->pr.b;
+            a.pf = phase_field(c);
+            a.meas = meas;
+            a.tick = !meas;
+            a.grav = grav;
+            const Collision<C> cp = collision(c);
+            step2d_launch(a, thermo(c), &cp, c->stream);
+            if (!meas) return;
+            const R* field = (const R*)a.field;
+            k_cross<L, R><<<cross_grid(c), 256, 0, c->stream>>>(field, c->cls, c->d, c->ctl, mp);
+            YoungStep ys{};
+            if (c->young_on) {
+                ys = young_step(c, mp);
+                k_young_step<L, R><<<cross_grid(c), 256, 0, c->stream>>>(field, c->cls, c->d, young_step_params(c, mp),
+                                                                        mp, c->ctl, c->ystep_counts);
+            }
+            k_finalize<L, R><<<1, 64, 0, c->stream>>>(field, c->ctl, c->d, mp, c->series, c->last, 1, ys, c->yseries);
+        }
     }
 
     // phase-field model (the split step): parameters, density, mu, collision
@@ -724,6 +780,12 @@ struct OpStep {
     }
 };
 template <class L, typename R, typename C>
+struct OpOne2d {
+    static void go(lbm_ctx* c, int src, const MeasureParams* mp, bool meas, bool grav) {
+        Run<L, R, C>::one2d_launches(c, src, *mp, meas, grav);
+    }
+};
+template <class L, typename R, typename C>
 struct OpFusedStep {
     static void go(lbm_ctx* c, int src, bool pull, int rsrc, const MeasureParams* mp, hipEvent_t* ev, int* kinds,
                    bool quiet = false) {
@@ -944,6 +1006,7 @@ lbm_status lbm_create(const lbm_config* cfg, lbm_ctx** out) {
                    c->d.nx % 64 == 0 && c->d.nx <= 1024 && c->d.ny % kFusedTY == 0 && zc >= 2 && c->d.nz % zc == 0 &&
                    5ull * (unsigned long long)N * elem < (1ull << 32);
     }
+    c->one2d = cfg->step_kernel == LBM_STEP_AUTO && c->dim == 2;
     c->pr.a = cfg->pr_a;
     c->pr.b = cfg->pr_b;
     c->pr.R = cfg->pr_R;
@@ -998,6 +1061,15 @@ lbm_status lbm_create(const lbm_config* cfg, lbm_ctx** out) {
         return s;
     }
     c->rho = c->rhob[0];
+    if (c->one2d) {
+        c->shape2d = shape2d_for(N, cfg->precision, model2d(c));
+        const std::vector<Tile2d> tl = tiles2d(&c->d, 1, c->shape2d);
+        c->ntiles = (int)tl.size();
+        if ((s = upload(c, &c->tiles, tl))) {
+            lbm_destroy(c);
+            return s;
+        }
+    }
     DevCtl h{};
     for (auto& k : h.m.keys) k[0] = k[1] = ~0ull;
     if (hipMemcpy(c->ctl, &h, sizeof h, hipMemcpyHostToDevice) != hipSuccess) {
@@ -1020,7 +1092,7 @@ lbm_status lbm_destroy(lbm_ctx* c) {
     void* ps[] = {c->f[0], c->f[1], c->rhob[0], c->rhob[1], c->gy, c->gz, c->gyz, c->force, c->sink, c->mu, c->cls, c->nbmask, c->bidx, c->l1_node, c->l2_node, c->b_node,
                   c->l1_mask, c->l2_mask, c->b_mask, c->l1_inv, c->l2_inv, c->b_q, c->ctl, c->last, c->series,
                   c->mass_part, c->mass_out, c->young_counts, c->ylast, c->yseries, c->ystep_counts,
-                  c->g[0], c->g[1], c->phi, c->curved};
+                  c->g[0], c->g[1], c->phi, c->curved, c->tiles};
     for (void* p : ps) dfree(p);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
     delete c;
@@ -1090,6 +1162,10 @@ lbm_status lbm_set_solid(lbm_ctx* c, const lbm_solid* prims, int n, const double
         c->n_curved = (int)cv.size();
     }
     c->n_fluid = g.n_fluid;
+    if (c->one2d) {
+        tiles2d_flags(c->tiles, c->ntiles, c->cls, model2d(c), c->shape2d, c->stream);
+        HIPCHK(c, hipGetLastError());
+    }
     // static wall chemical potential on the two solid layers; zero elsewhere
     {
         std::vector<double> muh((size_t)g.N, 0.0);
@@ -1370,6 +1446,52 @@ lbm_status lbm_step(lbm_ctx* c, int64_t nsteps, int measure_every, lbm_angle* se
         const int64_t r = t0 % measure_every;
         return r != 0 && measure_every - r >= kGraphSteps;
     };
+    // The single-launch step: a launch per step that measures nothing (whole
+    // windows of them as a captured graph, from buffer 0), the measurement's
+    // launches only on measure steps, which the host knows.  A state S_t is
+    // first brought to pull form by a split step.  A stream under capture
+    // takes the split step, whose launches decide on the device what they do.
+    bool one2d = c->one2d;
+    if (one2d) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            one2d = false;
+        }
+    }
+    while (one2d && done < nsteps) {
+        if (!c->fstar) {
+            eager();
+            continue;
+        }
+        const bool meas = measure_every > 0 && c->t % measure_every == 0;
+        int64_t run = nsteps - done;  // steps up to the next measure step
+        if (measure_every > 0 && measure_every - c->t % measure_every < run) run = measure_every - c->t % measure_every;
+        const bool on = c->t >= c->cfg.g_start_step;  // the body force acts throughout the window, or not at all in it
+        if (!meas && c->cur == 0 && run >= kGraphSteps && (on || c->t + kGraphSteps <= c->cfg.g_start_step)) {
+            hipGraphExec_t& ge = c->graph2d[on ? 1 : 0];
+            if (!ge) {
+                hipGraph_t g;
+                HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
+                for (int k = 0; k < kGraphSteps; ++k) dispatch<OpOne2d>(c, k & 1, &mp, false, on);
+                HIPCHK(c, hipStreamEndCapture(c->stream, &g));
+                const hipError_t e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
+                (void)hipGraphDestroy(g);
+                if (e != hipSuccess) {
+                    ge = nullptr;
+                    return fail(c, LBM_E_DEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
+                }
+            }
+            HIPCHK(c, hipGraphLaunch(ge, c->stream));
+            done += kGraphSteps;
+            c->t += kGraphSteps;
+            continue;
+        }
+        dispatch<OpOne2d>(c, c->cur, &mp, meas, on);
+        advance();
+        ++done;
+        ++c->t;
+    }
     while (done < nsteps && (!c->fstar || c->cur != 0 || c->rcur != 0 || nsteps - done < kGraphSteps)) eager();
     while (nsteps - done >= kGraphSteps) {
         const int gi = quiet_window(c->t) ? 1 : 0;

@@ -25,6 +25,7 @@
 #include "kernels.hpp"
 #include "lbm.h"
 #include "phasefield.hpp"
+#include "step2d.hpp"
 #include "young.hpp"
 
 using namespace lbm;
@@ -329,6 +330,12 @@ struct lbm_batch {
     double tune_ms = 0;
     hipGraphExec_t graph = nullptr;
     long long t = 0;
+    // the single-launch step of D2Q9 cases (step2d.hpp): its tiles and shape,
+    // and its captured windows without / with the body force
+    bool one2d = false;
+    Tile2d* tiles = nullptr;
+    int ntiles = 0, shape2d = 0;
+    hipGraphExec_t graph2d[2] = {nullptr, nullptr};
 };
 
 namespace {
@@ -497,6 +504,65 @@ struct BRun {
                                                         (R*)b->mu, b->cls, thermo(b));
     }
 
+    static int model2d(const lbm_batch* b) {
+        return b->pf ? M2_PHASE : (b->cfg.model == LBM_MODEL_PSEUDOPOTENTIAL ? M2_PSEUDO : M2_CHEM);
+    }
+    // the in-step Young force of a measure step: counts, then the options its finalize applies
+    static YoungStep young_counts(lbm_batch* b, int grid) {
+        YoungStep ys{};
+        if (!b->young_on) return ys;
+        kb_young_step<L, R><<<grid, 256, 0, b->stream>>>(b->items, b->nitems, b->dims, b->tile_w, mfield(b), b->cls,
+                                                         b->ystep_params, b->mp, b->slots, b->ctl, b->ystep_counts);
+        ys.on = 1;
+        ys.gamma = b->yopts.gamma;
+        ys.c1 = std::cos(b->yopts.theta1_deg * M_PI / 180.0);
+        ys.c2 = std::cos(b->yopts.theta2_deg * M_PI / 180.0);
+        ys.roughness = b->yopts.roughness;
+        ys.counts = b->ystep_counts;
+        ys.last = b->ylast;
+        return ys;
+    }
+    // One step of every case in a single launch (D2Q9, pull form) from f[src]
+    // into f[1 - src].  meas: a measure step, followed by the crossing search,
+    // the finalize and the count of the step; otherwise the launch counts it.
+    static void one2d(lbm_batch* b, int src, bool meas, bool grav, int grid) {
+        if constexpr (L::D == 2) {
+            Step2dArgs a{};
+            a.precision = b->cfg.precision;
+            a.model = model2d(b);
+            a.mrt = b->cfg.collision == LBM_MRT;
+            a.shape = b->shape2d;
+            a.tiles = b->tiles;
+            a.ntiles = b->ntiles;
+            a.N = b->Ntot;
+            a.fin = b->f[src];
+            a.fout = b->f[1 - src];
+            a.gin = b->g[src];
+            a.gout = b->g[1 - src];
+            a.field = b->pf ? b->phi : b->rho;
+            a.wall = b->pf ? b->phi : b->mu;
+            a.cls = b->cls;
+            a.bc = wall(b);
+            a.ctl = b->ctl;
+            a.slots = b->slots;
+            a.rho_m = b->rho_m;
+            a.inv_b = 1.0 / b->pr.b;
+            a.pf = b->pfp;
+            a.meas = meas;
+            a.tick = !meas;
+            a.grav = grav;
+            const Collision<C> cp = collision(b);
+            step2d_launch(a, thermo(b), &cp, b->stream);
+            if (!meas) return;
+            const R* mf = mfield(b);
+            kb_cross<L, R><<<grid, 256, 0, b->stream>>>(b->items, b->nitems, b->dims, b->tile_w, mf, b->cls, b->ctl,
+                                                        b->slots, b->mp);
+            const YoungStep ys = young_counts(b, grid);
+            kb_finalize<L, R><<<b->ncases, 64, 0, b->stream>>>(mf, b->ctl, b->dims, b->mp, b->slots, b->last, ys);
+            kb_tick<<<1, 64, 0, b->stream>>>(b->ctl);
+        }
+    }
+
     // one step from f[src] (pull form if pull) into f[1 - src]
     static void step(lbm_batch* b, int src, bool pull, int grid, hipEvent_t* ev = nullptr) {
         if (b->pf) {
@@ -516,19 +582,7 @@ struct BRun {
         const R* mf = mfield(b);
         kb_cross<L, R><<<grid, 256, 0, b->stream>>>(b->items, b->nitems, b->dims, b->tile_w, mf, b->cls, b->ctl, b->slots,
                                                     b->mp);
-        YoungStep ys{};
-        if (b->young_on) {
-            kb_young_step<L, R><<<grid, 256, 0, b->stream>>>(b->items, b->nitems, b->dims, b->tile_w, mf, b->cls,
-                                                             b->ystep_params, b->mp, b->slots, b->ctl,
-                                                             b->ystep_counts);
-            ys.on = 1;
-            ys.gamma = b->yopts.gamma;
-            ys.c1 = std::cos(b->yopts.theta1_deg * M_PI / 180.0);
-            ys.c2 = std::cos(b->yopts.theta2_deg * M_PI / 180.0);
-            ys.roughness = b->yopts.roughness;
-            ys.counts = b->ystep_counts;
-            ys.last = b->ylast;
-        }
+        const YoungStep ys = young_counts(b, grid);
         const R* fin = (const R*)b->f[src];
         R* fout = (R*)b->f[1 - src];
         const WallBC bc = wall(b);
@@ -613,6 +667,12 @@ struct BStep {
     static void go(lbm_batch* b, int src, bool pull, int grid) { BRun<L, R, C>::step(b, src, pull, grid); }
 };
 template <class L, typename R, typename C>
+struct BOne2d {
+    static void go(lbm_batch* b, int src, bool meas, bool grav, int grid) {
+        BRun<L, R, C>::one2d(b, src, meas, grav, grid);
+    }
+};
+template <class L, typename R, typename C>
 struct BStepTimed {
     static void go(lbm_batch* b, int src, bool pull, int grid, hipEvent_t* ev) {
         BRun<L, R, C>::step(b, src, pull, grid, ev);
@@ -666,8 +726,10 @@ struct BYoung {
 int grid_of(const lbm_batch* b) { return b->bpc * b->cus; }
 
 void drop_graph(lbm_batch* b) {
-    if (b->graph) (void)hipGraphExecDestroy(b->graph);
-    b->graph = nullptr;
+    for (hipGraphExec_t* g : {&b->graph, &b->graph2d[0], &b->graph2d[1]}) {
+        if (*g) (void)hipGraphExecDestroy(*g);
+        *g = nullptr;
+    }
 }
 
 // --- autotuner: time candidate (tile width, workgroups per CU) pairs ---------
@@ -817,7 +879,7 @@ lbm_status lbm_batch_destroy(lbm_batch* b) {
     drop_graph(b);
     void* ps[] = {b->dims, b->mp,   b->slots, b->last, b->ctl,  b->f[0], b->f[1], b->rho,  b->mu,   b->inv,
                   b->bq,   b->cls,  b->nbmask, b->fmask, b->bidx, b->fcase, b->fnode, b->items,
-                  b->yparams, b->ycounts, b->ystep_params, b->ystep_counts, b->ylast, b->g[0], b->g[1], b->phi};
+                  b->yparams, b->ycounts, b->ystep_params, b->ystep_counts, b->ylast, b->g[0], b->g[1], b->phi, b->tiles};
     for (void* p : ps)
         if (p) (void)hipFree(p);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
@@ -1054,6 +1116,18 @@ lbm_status lbm_batch_create(const lbm_config* base, const lbm_case* cases, int n
         lbm_batch_destroy(b);
         return s;
     }
+    const int model = b->pf ? M2_PHASE : (sc ? M2_PSEUDO : M2_CHEM);
+    b->one2d = b->dim == 2 && base->step_kernel != LBM_STEP_SPLIT;
+    if (b->one2d) {
+        b->shape2d = shape2d_for(b->n_nodes, base->precision, model);
+        const std::vector<Tile2d> tl = tiles2d(b->dims_h.data(), ncases, b->shape2d);
+        b->ntiles = (int)tl.size();
+        if ((s = bupload(b, &b->tiles, tl))) {
+            lbm_batch_destroy(b);
+            return s;
+        }
+        tiles2d_flags(b->tiles, b->ntiles, b->cls, model, b->shape2d, b->stream);
+    }
     DevCtl h{};
     for (auto& k : h.m.keys) k[0] = k[1] = ~0ull;
     if (hipMemcpy(b->ctl, &h, sizeof h, hipMemcpyHostToDevice) != hipSuccess) {
@@ -1113,6 +1187,49 @@ lbm_status lbm_batch_step(lbm_batch* b, int64_t nsteps, int measure_every) {
         ++done;
         ++b->t;
     };
+    // the single-launch step, as lbm_step runs it: captured windows of steps
+    // that measure nothing, the measurement's launches on measure steps only
+    bool one2d = b->one2d;
+    if (one2d) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(b->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            one2d = false;
+        }
+    }
+    while (one2d && done < nsteps) {
+        if (!b->fstar) {
+            eager();
+            continue;
+        }
+        const bool meas = measure_every > 0 && b->t % measure_every == 0;
+        int64_t run = nsteps - done;
+        if (measure_every > 0 && measure_every - b->t % measure_every < run) run = measure_every - b->t % measure_every;
+        const bool on = b->t >= b->cfg.g_start_step;
+        if (!meas && b->cur == 0 && run >= kBatchGraphSteps && (on || b->t + kBatchGraphSteps <= b->cfg.g_start_step)) {
+            hipGraphExec_t& ge = b->graph2d[on ? 1 : 0];
+            if (!ge) {
+                hipGraph_t g;
+                BCHK(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
+                for (int k = 0; k < kBatchGraphSteps; ++k) bdispatch<BOne2d>(b, k & 1, false, on, grid_of(b));
+                BCHK(b, hipStreamEndCapture(b->stream, &g));
+                const hipError_t e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
+                (void)hipGraphDestroy(g);
+                if (e != hipSuccess) {
+                    ge = nullptr;
+                    return bfail(b, LBM_E_DEVICE, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
+                }
+            }
+            BCHK(b, hipGraphLaunch(ge, b->stream));
+            done += kBatchGraphSteps;
+            b->t += kBatchGraphSteps;
+            continue;
+        }
+        bdispatch<BOne2d>(b, b->cur, meas, on, grid_of(b));
+        b->cur ^= 1;
+        ++done;
+        ++b->t;
+    }
     while (done < nsteps && (!b->fstar || b->cur != 0 || nsteps - done < kBatchGraphSteps)) eager();
     if (nsteps - done >= kBatchGraphSteps) {
         if (!b->graph) {

@@ -956,15 +956,20 @@ __device__ __forceinline__ void feq_all(C rs, C ax, C ay, C az, C out[L::Q]) {
     }
 }
 
-// The post-collision populations of one node into fo (storage type).
-template <class L, typename R, typename C, bool MRT>
+// The post-collision populations of one node into fo (storage type).  HAVE_RD:
+// the density moment is given (the caller has summed it already, as below).
+template <class L, typename R, typename C, bool MRT, bool HAVE_RD = false>
 __device__ __forceinline__ void collide_values(const R S[L::Q], C Fx, C Fy, C Fz, const Collision<C>& cp,
-                                               R fo[L::Q]) {
+                                               R fo[L::Q], double rd_given = 0.0) {
     // the density moment of S (Eq. 2 argument) in double: the rest population
     // below takes the remainder of it
     double rd = 0.0;
+    if constexpr (HAVE_RD) {
+        rd = rd_given;
+    } else {
 #pragma unroll
-    for (int i = 0; i < L::Q; ++i) rd += (double)S[i];
+        for (int i = 0; i < L::Q; ++i) rd += (double)S[i];
+    }
     C rs, ux, uy, uz, vx, vy, vz;
     if constexpr (sizeof(C) == 8) {
         typedef double D;
