@@ -559,14 +559,14 @@ struct Run {
                             const Collision<C>& cp) {
         const dim3 grd((unsigned)((c->d.ny / kFusedTY) * (c->d.nz / c->fzc)), 1, 1), blk((unsigned)c->d.nx, 1, 1);
         // workgroup = one row of nx threads; the launch bound follows it
-        if (c->d.nx <= 256)
-            k_step<R, C, PULL, MRT, SC, kFusedTY, 256><<<grd, blk, 0, c->stream>>>(
-                fin, fout, rho, (const R*)c->mu, (const R*)c->force, rnext, (R*)c->gy, (R*)c->gz, (R*)c->gyz, c->cls,
-                c->d, bc, cp, c->ctl, c->fzc, (R*)c->sink);
-        else
-            k_step<R, C, PULL, MRT, SC, kFusedTY, 1024><<<grd, blk, 0, c->stream>>>(
-                fin, fout, rho, (const R*)c->mu, (const R*)c->force, rnext, (R*)c->gy, (R*)c->gz, (R*)c->gyz, c->cls,
-                c->d, bc, cp, c->ctl, c->fzc, (R*)c->sink);
+#define LBM_K_STEP(NX)                                                                                          \
+    k_step<R, C, PULL, MRT, SC, kFusedTY, NX><<<grd, blk, 0, c->stream>>>(                                       \
+        fin, fout, rho, (const R*)c->mu, (const R*)c->force, rnext, (R*)c->gy, (R*)c->gz, (R*)c->gyz, c->cls, c->d, \
+        bc, cp, c->ctl, c->fzc, (R*)c->sink)
+        if (c->d.nx <= 256) LBM_K_STEP(256);
+        else if (c->d.nx <= 384) LBM_K_STEP(384);
+        else LBM_K_STEP(1024);
+#undef LBM_K_STEP
     }
     // the force of the current state (rho, mu) into c->force
     static void launch_force(lbm_ctx* c, const R* rho) {
@@ -993,8 +993,12 @@ lbm_status lbm_create(const lbm_config* cfg, lbm_ctx** out) {
         // 0.574, 0.584, 0.570 ms and the ghost sums 0.025, 0.022, 0.020 ms;
         // without the ring 64 planes (one workgroup per CU) took 0.729 ms, and
         // at 512^3 16 and 32 planes 4.61 and 4.59 ms
+        // Rows of 257 to 384 nodes (six waves per workgroup, two workgroups per
+        // CU: 512 at a time) start at 16: at 384 x 320 x 256 the 640 workgroups
+        // of 32 planes run in two rounds, the second a quarter full (8, 16, 32
+        // planes: 63.1, 61.8, 67.0 ms per 40 steps).
         const char* e = std::getenv("LBM_FUSED_ZC");
-        int zc = e ? std::atoi(e) : 32;
+        int zc = e ? std::atoi(e) : (c->d.nx > 256 && c->d.nx <= 384 ? 16 : 32);
         while (zc > 2 && c->d.nz % zc) zc >>= 1;
         if (!e)
             while (zc > 8 && (long long)(c->d.ny / kFusedTY) * (c->d.nz / zc) < 512) zc >>= 1;

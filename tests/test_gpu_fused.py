@@ -146,6 +146,26 @@ def test_one_pass_fp32_stencil_ring_shapes(n, wall, collision):
     assert e <= 1e-6
 
 
+@pytest.mark.parametrize("nx", [320, 384])
+@pytest.mark.parametrize("zc", ["16", None])
+@pytest.mark.parametrize("precision,tol", [(G.LBM_F32, 1e-6), (G.LBM_F64, 1e-12)])
+def test_one_pass_rows_of_five_and_six_waves(nx, zc, precision, tol, monkeypatch):
+    # rows of 257 to 384 nodes have a kernel of their own (ring of 48 KB, FP32
+    # only): x neighbours across waves and the periodic row end, both plane
+    # depths of its rule (16, and 8 on a small lattice)
+    if zc:
+        monkeypatch.setenv("LBM_FUSED_ZC", zc)
+    wl = case((nx, 16, 32), (0, 1, 1))
+    gp = gpu_lattice(wl, precision, "bgk", **SMALL)
+    assert is_fused(gp)
+    o = oracle_lattice(wl, "bgk", **SMALL)
+    o.step(1)
+    gp.step(29)
+    o.step(29)
+    o.update_derived()
+    assert rel_err(gp.rho, o.rho, o.cls <= 2) <= tol
+
+
 def test_one_pass_in_step_measurement_matches_oracle():
     wl = case((128, 24, 40), (1, 1, 1), r=9.1, drop=8.0)
     gp = gpu_lattice(wl, G.LBM_F64, "bgk", **SMALL)
