@@ -558,13 +558,28 @@ struct Run {
     static void launch_step(lbm_ctx* c, const R* fin, R* fout, const R* rho, R* rnext, const WallBC& bc,
                             const Collision<C>& cp) {
         const dim3 grd((unsigned)((c->d.ny / kFusedTY) * (c->d.nz / c->fzc)), 1, 1), blk((unsigned)c->d.nx, 1, 1);
-        // workgroup = one row of nx threads; the launch bound follows it
+        // Workgroup = one row of nx threads; the launch bound follows it.  In
+        // double the bound of 1024 threads (128 registers) spills up to 340
+        // bytes a lane, bounds of 384 and 512 (up to 206 registers) nothing: at
+        // 384 x 320 x 256, ms per launch before and after, F64 MRT 7.2 and 2.7,
+        // BGK 6.4 and 2.7, mixed MRT 5.3 and 1.8, BGK 2.1 and 1.35; at 512 x
+        // 256 x 128 F64 MRT 3.5 and 1.26, mixed 2.5 and 0.75.  In float nothing
+        // spills at 1024 and smaller bounds give nothing (512 x 256 x 128: 0.612
+        // at 1024, 0.620 at 512), except where they carry the stencil ring
+        // (BGK, six waves a row).
 #define LBM_K_STEP(NX)                                                                                          \
     k_step<R, C, PULL, MRT, SC, kFusedTY, NX><<<grd, blk, 0, c->stream>>>(                                       \
         fin, fout, rho, (const R*)c->mu, (const R*)c->force, rnext, (R*)c->gy, (R*)c->gz, (R*)c->gyz, c->cls, c->d, \
         bc, cp, c->ctl, c->fzc, (R*)c->sink)
         if (c->d.nx <= 256) LBM_K_STEP(256);
-        else if (c->d.nx <= 384) LBM_K_STEP(384);
+        else if constexpr (sizeof(C) == 8) {
+            if (c->d.nx <= 384) LBM_K_STEP(384);
+            else if (c->d.nx <= 512) LBM_K_STEP(512);
+            else LBM_K_STEP(1024);
+        } else if constexpr (!MRT && !SC) {
+            if (c->d.nx > 320 && c->d.nx <= 384) LBM_K_STEP(384);
+            else LBM_K_STEP(1024);
+        }
         else LBM_K_STEP(1024);
 #undef LBM_K_STEP
     }
@@ -993,10 +1008,11 @@ lbm_status lbm_create(const lbm_config* cfg, lbm_ctx** out) {
         // 0.574, 0.584, 0.570 ms and the ghost sums 0.025, 0.022, 0.020 ms;
         // without the ring 64 planes (one workgroup per CU) took 0.729 ms, and
         // at 512^3 16 and 32 planes 4.61 and 4.59 ms
-        // Rows of 257 to 384 nodes (six waves per workgroup, two workgroups per
-        // CU: 512 at a time) start at 16: at 384 x 320 x 256 the 640 workgroups
-        // of 32 planes run in two rounds, the second a quarter full (8, 16, 32
-        // planes: 63.1, 61.8, 67.0 ms per 40 steps).
+        // Rows of 257 to 384 nodes (two workgroups of five or six waves per CU:
+        // 512 at a time) start at 16: the 640 workgroups of 32 planes at 384 x
+        // 320 x 256 run in two rounds, the second a quarter full (the walk over
+        // 8, 16, 32 planes: FP32 MRT 1.37, 1.41, 1.48 ms, BGK 1.30, 1.25, 1.39,
+        // F64 MRT 2.77, 2.71, 2.97; at 320 x 320 x 256 MRT 1.17, 1.09, 1.28).
         const char* e = std::getenv("LBM_FUSED_ZC");
         int zc = e ? std::atoi(e) : (c->d.nx > 256 && c->d.nx <= 384 ? 16 : 32);
         while (zc > 2 && c->d.nz % zc) zc >>= 1;

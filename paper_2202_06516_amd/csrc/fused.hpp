@@ -238,12 +238,13 @@ __global__ void __launch_bounds__(NX) k_step(const R* __restrict__ fin, R* __res
     // into the slot of plane z - 2 (no longer needed by its row).  A slot is
     // written two planes before another thread reads it and overwritten two
     // planes after, with a barrier at the end of every plane in between.
-    // FP32 storage and rows of up to 384 nodes (32 KB at 256, 48 KB at 384;
-    // there, with the accumulators sized for the row as well, the step of 384 x
-    // 320 x 256 nodes takes 1.46 ms instead of 1.53 at 16 planes per
-    // workgroup).  (Rows of 512 in a 512-thread variant with the ring ran no
-    // faster at 512^3.)
-    constexpr bool RING = !SC && sizeof(R) == 4 && NX <= 384;
+    // FP32 storage and rows of up to 256 nodes (32 KB); with FP32 BGK also rows
+    // of 321 to 384 (48 KB, the NX = 384 kernel).  Measured there, without and
+    // with the ring, ms per launch: 384 x 320 x 256 BGK 1.35 and 1.25, MRT 1.41
+    // and 1.43; 384 x 256 x 128 BGK 0.458 and 0.463, MRT 0.485 and 0.577; rows
+    // of 320 BGK 0.387 and 0.430, MRT 0.42 and 0.56.  (Rows of 512 with the
+    // ring ran no faster at 512^3.)
+    constexpr bool RING = !SC && sizeof(R) == 4 && (NX <= 256 || (NX == 384 && !MRT && sizeof(C) == 4));
     __shared__ R ring[RING ? 4 : 1][TY][2][RING ? NX : 1];
 #pragma unroll
     for (int k = 0; k < TY + 2; ++k) acc[k][0][x] = acc[k][1][x] = acc[k][2][x] = C(0);

@@ -146,19 +146,20 @@ def test_one_pass_fp32_stencil_ring_shapes(n, wall, collision):
     assert e <= 1e-6
 
 
-@pytest.mark.parametrize("nx", [320, 384])
-@pytest.mark.parametrize("zc", ["16", None])
-@pytest.mark.parametrize("precision,tol", [(G.LBM_F32, 1e-6), (G.LBM_F64, 1e-12)])
-def test_one_pass_rows_of_five_and_six_waves(nx, zc, precision, tol, monkeypatch):
-    # rows of 257 to 384 nodes have a kernel of their own (ring of 48 KB, FP32
-    # only): x neighbours across waves and the periodic row end, both plane
-    # depths of its rule (16, and 8 on a small lattice)
+@pytest.mark.parametrize("nx,zc", [(320, None), (384, "16"), (448, None), (512, "16")])
+@pytest.mark.parametrize("collision", ["bgk", "mrt"])
+@pytest.mark.parametrize("precision,tol", [(G.LBM_F32, 1e-6), (G.LBM_F32_MIXED, 3e-7), (G.LBM_F64, 1e-12)])
+def test_one_pass_rows_of_five_to_eight_waves(nx, zc, collision, precision, tol, monkeypatch):
+    # double arithmetic has a kernel each for rows of up to 384 and 512 nodes,
+    # FP32 BGK one with the stencil ring for 321 to 384: x neighbours across
+    # waves and the periodic row end, planes per workgroup of 8 (small lattice)
+    # and 16
     if zc:
         monkeypatch.setenv("LBM_FUSED_ZC", zc)
     wl = case((nx, 16, 32), (0, 1, 1))
-    gp = gpu_lattice(wl, precision, "bgk", **SMALL)
+    gp = gpu_lattice(wl, precision, collision, **SMALL)
     assert is_fused(gp)
-    o = oracle_lattice(wl, "bgk", **SMALL)
+    o = oracle_lattice(wl, collision, **SMALL)
     o.step(1)
     gp.step(29)
     o.step(29)
