@@ -222,7 +222,22 @@ void tile_dims(Dims& d, int dim) {
         const char* e = std::getenv("LBM_ZCHUNK");
         const int zc = dim == 3 ? (e ? std::atoi(e) : 8) : 1;
         d.zc = zc < 1 ? 1 : zc;
-        d.nblocks_zc = (unsigned)d.tx * (unsigned)d.ty * (unsigned)((d.nz + d.zc - 1) / d.zc);
+    }
+    {
+        // Runs of 256 consecutive nodes wherever the tiles leave lanes without a
+        // node (else a tile is such a run already).  Tiles and runs, us per step
+        // (split step, FP32 MRT): 150 x 118 x 97 (41% of the lanes without a
+        // node) 145 and 125; 160^3 (38%) 348 and 286; 200 x 150 x 128 (22%) 307
+        // and 246; 240 x 240 x 120 (6%) 454 and 428; 128 x 130 x 128 (none) 145
+        // and 144.  The batches' padded rows and lattices of 2^31 nodes (the
+        // divisions are for less) keep the tiles.
+        const long long nodes = (long long)d.nx * d.ny * d.nz;
+        d.runs = d.px == d.nx && nodes < (1ll << 31) - 256 && 256ll * d.nblocks != nodes;
+        d.rx = 0xffffffffu / (unsigned)d.nx;
+        d.ry = 0xffffffffu / (unsigned)d.ny;
+        d.nwg = d.runs ? (unsigned)((nodes + 255) / 256) : d.nblocks;
+        d.wg_plane = d.runs ? (unsigned)(((long long)d.nx * d.ny + 255) / 256) : (unsigned)d.tx * (unsigned)d.ty;
+        d.nblocks_zc = d.wg_plane * (unsigned)((d.nz + d.zc - 1) / d.zc);
     }
     {
         const char* e = std::getenv("LBM_XCD_REMAP");
@@ -274,9 +289,9 @@ struct Run {
         cp.sc_G = g.sc_G;
         return cp;
     }
-    static dim3 grid(const lbm_ctx* c) { return dim3(c->d.nblocks, 1, 1); }
+    static dim3 grid(const lbm_ctx* c) { return dim3(c->d.nwg, 1, 1); }
     // the z-chunked chemical-potential kernel
-    static dim3 zgrid(const lbm_ctx* c) { return dim3(c->d.zc > 1 ? c->d.nblocks_zc : c->d.nblocks, 1, 1); }
+    static dim3 zgrid(const lbm_ctx* c) { return dim3(c->d.nblocks_zc, 1, 1); }
     // the crossing search walks the tiles in a grid-stride loop
     static dim3 cross_grid(const lbm_ctx* c) { return dim3(c->d.nblocks < 2048u ? c->d.nblocks : 2048u, 1, 1); }
 

@@ -20,8 +20,9 @@
 // into mu once, when the solids are set.
 //
 // Every per-node computation is a device function ("body") shared by two kinds
-// of launch: one lattice tiled by 256-thread workgroups (one 256-node row
-// segment, or 128 x 2 / 64 x 4 nodes on narrower lattices), or many packed
+// of launch: one lattice cut into 256-thread workgroups (a run of 256
+// consecutive nodes; the measurement's kernels, which walk a box, in tiles of
+// 256 x 1, 128 x 2 or 64 x 4 nodes), or many packed
 // lattices walked by a persistent work list (the batched solver).  A lattice
 // lives at offset off of the packed arrays; N is the population stride.
 //
@@ -51,7 +52,11 @@ struct Dims {
     int xcd_remap;       // 1: contiguous tile ranges per XCD
     int tws;             // log2 of the tile width: tiles of 2^tws x 256 / 2^tws nodes (one per 256-thread workgroup)
     int zc;              // planes per workgroup of the z-chunked chemical-potential kernel (<= 1: one plane)
-    unsigned nblocks_zc; // tx * ty * ceil(nz / zc) workgroups of that kernel
+    unsigned nblocks_zc; // workgroups of that kernel: tiles of a plane * ceil(nz / zc)
+    int runs;            // 1: a workgroup of the per-node kernels takes a run of 256 consecutive nodes, not a tile
+    unsigned nwg;        // workgroups of the per-node kernels (nblocks, or ceil(nx ny nz / 256) with runs)
+    unsigned wg_plane;   // workgroups per plane of the z-chunked kernels (tx * ty, or ceil(nx ny / 256) with runs)
+    unsigned rx, ry;     // floor((2^32 - 1) / nx), floor((2^32 - 1) / ny)
 };
 
 __device__ __forceinline__ long long nid(const Dims& d, int x, int y, int z) {
@@ -70,15 +75,39 @@ __device__ __forceinline__ void tile_coords(const Dims& d, unsigned t, int& x, i
     z = (int)(rest / (unsigned)d.ty);
 }
 
-// Node of this thread.  Workgroups are dispatched to the 8 XCDs round-robin
-// by workgroup id; with xcd_remap each XCD receives one contiguous range of
-// tiles (a slab of z planes), so the stencil neighbours of a tile sit in the
-// same L2.  The map is a bijection of [0, nblocks).
+// n / m and n % m for n < 2^31 with rm = floor((2^32 - 1) / m): the product
+// falls short of the quotient by less than one.
+__device__ __forceinline__ void divmod(unsigned n, unsigned m, unsigned rm, unsigned& q, unsigned& r) {
+    q = __umulhi(n, rm);
+    r = n - q * m;
+    if (r >= m) {
+        r -= m;
+        ++q;
+    }
+}
+
+// Workgroup w of n in the order of the tiles.  Workgroups are dispatched to
+// the 8 XCDs round-robin by workgroup id; with xcd_remap each XCD receives one
+// contiguous range of tiles (a slab of z planes), so the stencil neighbours of
+// a tile sit in the same L2.  The map is a bijection of [0, n).
+__device__ __forceinline__ unsigned tile_of(const Dims& d, unsigned w, unsigned n) {
+    if (!d.xcd_remap) return w;
+    const unsigned q = n >> 3, r = n & 7u, xcd = w & 7u, loc = w >> 3;
+    return (xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q) + loc;
+}
+
+// Node of this thread (x >= nx or y >= ny: none).  With runs the workgroup
+// holds 256 consecutive nodes, wherever rows and planes end.
 __device__ __forceinline__ void tile_node(const Dims& d, int& x, int& y, int& z) {
-    unsigned t = blockIdx.x;
-    if (d.xcd_remap) {
-        const unsigned q = d.nblocks >> 3, r = d.nblocks & 7u, xcd = t & 7u, loc = t >> 3;
-        t = (xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q) + loc;
+    const unsigned t = tile_of(d, blockIdx.x, d.nwg);
+    if (d.runs) {
+        unsigned row, xx, yy, zz;
+        divmod(t * 256u + threadIdx.x, (unsigned)d.nx, d.rx, row, xx);
+        divmod(row, (unsigned)d.ny, d.ry, zz, yy);
+        x = (int)xx;
+        y = zz < (unsigned)d.nz ? (int)yy : d.ny;
+        z = (int)zz;
+        return;
     }
     tile_coords(d, t, x, y, z);
 }
@@ -89,13 +118,17 @@ __device__ __forceinline__ void tile_node(const Dims& d, int& x, int& y, int& z)
 // stencil are the ones it read an iteration before.  (Chunking the collision
 // the same way made it slower: 0.69-0.77 ms instead of 0.61 ms at 256^3.)
 __device__ __forceinline__ void tile_node_zc(const Dims& d, int& x, int& y, int& z0) {
-    unsigned t = blockIdx.x;
-    if (d.xcd_remap) {
-        const unsigned q = d.nblocks_zc >> 3, r = d.nblocks_zc & 7u, xcd = t & 7u, loc = t >> 3;
-        t = (xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q) + loc;
-    }
+    const unsigned t = tile_of(d, blockIdx.x, d.nblocks_zc);
     int zi;
-    tile_coords(d, t, x, y, zi);
+    if (d.runs) {
+        zi = (int)(t / d.wg_plane);
+        unsigned yy, xx;
+        divmod((t - (unsigned)zi * d.wg_plane) * 256u + threadIdx.x, (unsigned)d.nx, d.rx, yy, xx);
+        x = (int)xx;
+        y = (int)yy;  // >= ny past the plane's last node
+    } else {
+        tile_coords(d, t, x, y, zi);
+    }
     z0 = zi * d.zc;
 }
 
