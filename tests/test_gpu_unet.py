@@ -106,6 +106,17 @@ def test_small_networks_match_the_oracle(levels, base, H, W, n):
     check_against_oracle(levels, base, H, W, n, seed=100 + levels * 10 + n)
 
 
+@pytest.mark.parametrize("levels,base,H,W,n", [
+    (1, 16, 130, 130, 9),   # 891 convolution tiles: two per workgroup, the last workgroup one; rows and columns ragged
+    (2, 32, 102, 124, 11),  # 572 tiles of two channel chunks, two per workgroup; 64-pixel tiles, last row half empty
+    (2, 32, 6, 40, 3),      # level 1: 20 pixels, tiles of 32 pixels by 64 channels
+    (2, 64, 8, 96, 2),      # tiles of 32 pixels by 64 channels in both passes, four chunks
+    (2, 16, 14, 66, 2),     # a chunk of 16 upsampled and 16 skip channels
+])
+def test_convolution_tiles_match_the_oracle(levels, base, H, W, n):
+    check_against_oracle(levels, base, H, W, n, seed=200 + levels * 10 + n)
+
+
 def test_fewer_samples_than_the_batch():
     check_against_oracle(2, 16, 16, 16, 2, seed=7, batch=5)
 
