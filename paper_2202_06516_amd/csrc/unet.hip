@@ -60,6 +60,7 @@ __device__ __forceinline__ bf16x8 ld8(const bf16* p) { return *reinterpret_cast<
 // which leaves lane i holding row i at k = 8 g .. 8 g + 7: the layout the
 // MFMA takes.  p = &stage[0][row0]; stride = elements per k row.
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 __device__ __forceinline__ bf16x8 ld_tr8(const bf16* p, int stride, int lane) {
     const int t = lane & 15, g = lane >> 4;
@@ -77,10 +78,15 @@ __device__ __forceinline__ bf16x8 zero8() {
     for (int j = 0; j < 8; ++j) v[j] = (bf16)0.f;
     return v;
 }
+// v where the ReLU output m is positive, else 0 (m is never NaN): on pairs of
+// 16-bit words, which order as integers do where they are positive
 __device__ __forceinline__ bf16x8 masked8(bf16x8 v, bf16x8 m) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (!((float)m[j] > 0.f)) v[j] = (bf16)0.f;
+    s16x8 a, b;
+    __builtin_memcpy(&a, &v, 16);
+    __builtin_memcpy(&b, &m, 16);
+    const s16x8 on = __builtin_elementwise_min(__builtin_elementwise_max(b, (s16x8)0), (s16x8)1);
+    a &= (s16x8)0 - on;
+    __builtin_memcpy(&v, &a, 16);
     return v;
 }
 
@@ -454,6 +460,10 @@ __global__ void __launch_bounds__(256) k_gemm(LA A, LB B, EPI epi, i64 M, i64 N,
                 epi(m0 + wm + i * 16 + (lane >> 4) * 4 + q, n0 + wn + j * 16 + (lane & 15), acc[i][j][q]);
 }
 
+// Barrier for what the threads exchange through LDS: waits for this wave's LDS
+// operations only, so that global loads issued ahead stay in flight.
+__device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // ---------------------------------------------------------------------------
 // Weight gradient of a 3x3 convolution with all nine taps in one workgroup
 // ---------------------------------------------------------------------------
@@ -469,23 +479,29 @@ __global__ void __launch_bounds__(256) k_gemm(LA A, LB B, EPI epi, i64 M, i64 N,
 // (deterministic).  Within a group the W waves share the BM = 16 TM output
 // channels and split the BN = 16 TN W input channels, each 16 TM x 16 TN of
 // (co, c) for every tap; both operands enter the MFMA through the transposing
-// LDS read.
+// LDS read.  One workgroup per CU: what bounds it is the wait for a segment's
+// loads, issued one segment ahead (55% of the wave cycles; LDS and VALU are
+// active a quarter of the time each).  Loads that do not branch or wait for the
+// mask, offsets formed once and one LDS pass per group in the final sum took
+// 64 -> 64 channels of 8 x 128 x 128 from 42.6 to 35.0 us and 32 -> 32 of 8 x
+// 256 x 256 from 41.0 to 29.7 us (means over the network's launches).
 constexpr int SEG = 32;  // pixels per segment = one MFMA K step
 
 template <int TM, int TN, int W, int G>
 __global__ void __launch_bounds__(64 * W * G) k_wgrad3x3(const bf16* __restrict__ dY, const bf16* __restrict__ Y,
                                                       const bf16* __restrict__ X1, const bf16* __restrict__ X2,
-                                                      int C1, int C2, int Co, Grid g, int segs_row, int nsegs,
-                                                      int spc, float* __restrict__ P) {
+                                                      int C1, int C2, int Co, Grid g, FastDiv fS,
+                                                      int segs_row, int nsegs, int spc, float* __restrict__ P) {
     constexpr int NT = 64 * W;  // threads per group
     constexpr int BM = 16 * TM, BN = 16 * TN * W, DC = BM + 8, XC = BN + 8, XW = SEG + 2;
     constexpr int NVD = SEG * BM / 8, NVX = 3 * XW * BN / 8;
     constexpr int RD = (NVD + NT - 1) / NT, RX = (NVX + NT - 1) / NT;
     constexpr int DS = SEG * DC, XS = 3 * XW * XC;  // elements per stage
     __shared__ __attribute__((aligned(16))) bf16 lds[G * 2 * (DS + XS)];
-    static_assert(BM * BN * 4 <= G * 2 * (DS + XS) * 2, "reduction buffer");
+    static_assert(9 * BM * BN * 4 <= G * 2 * (DS + XS) * 2, "reduction buffer");
 
-    const int q = threadIdx.x / NT, tid = threadIdx.x % NT, lane = tid & 63, wave = tid >> 6;
+    const int q = __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);  // the same for a wave
+    const int tid = threadIdx.x % NT, lane = tid & 63, wave = tid >> 6;
     bf16* Ds = lds + q * 2 * (DS + XS);  // this group's two stages: Ds[st], then Xs[st]
     bf16* Xs = Ds + 2 * DS;
     const int co0 = blockIdx.x * BM, c0 = blockIdx.y * BN, Cp = C1 + C2;
@@ -503,54 +519,86 @@ __global__ void __launch_bounds__(64 * W * G) k_wgrad3x3(const bf16* __restrict_
             for (int j = 0; j < TN; ++j) acc[t][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     float bsum = 0.f;
 
-    bf16x8 rd[RD], rx[RX];
+    // A thread's vectors keep their channels and their place in the stage, so
+    // their offsets from the segment's first pixel are formed once (a vector
+    // past the stage or the channels: some element in range, never kept).  A
+    // bit per vector says which are kept (X from bit 0, dY from bit 16): all of
+    // them in segments whose neighbourhood lies inside the image.  The others
+    // load from the segment's first pixel where they would leave the image.
+    // The ReLU mask is applied when the vectors are staged.
+    static_assert(NT % (BN / 8) == 0 && XW * BN / 8 % (BN / 8) == 0 && NT % (BM / 8) == 0, "a thread's channels");
+    static_assert(RX <= 16 && RD <= 16, "one bit per vector");
+    const int cx = c0 + (tid % (BN / 8)) * 8, cd = co0 + (tid % (BM / 8)) * 8;
+    const bool second = cx >= C1 && cx < Cp;
+    const bf16* Xb = second ? X2 + (cx - C1) : cx < C1 ? X1 + cx : X1;
+    const int Cs = second ? C2 : C1;
+    const bf16* Db = cd < Co ? dY + cd : dY;
+    const bf16* Yb = cd < Co ? Y + cd : Y;
+    int ox[RX], od[RD];
+    uint32_t inner = 0;
+#pragma unroll
+    for (int r = 0; r < RX; ++r) {
+        const int v = tid + NT * r, dr = v / (XW * BN / 8), j = (v - dr * (XW * BN / 8)) / (BN / 8);
+        const bool ok = NVX % NT == 0 || v < NVX;
+        ox[r] = ok ? ((dr - 1) * g.W + j - 1) * Cs : 0;
+        inner |= (ok && cx < Cp ? 1u : 0u) << r;
+    }
+#pragma unroll
+    for (int r = 0; r < RD; ++r) {
+        const int v = tid + NT * r;
+        const bool ok = NVD % NT == 0 || v < NVD;
+        od[r] = ok ? v / (BM / 8) * Co : 0;
+        inner |= (ok && cd < Co ? 0x10000u : 0u) << r;
+    }
+    bf16x8 rd[RD], rm[RD], rx[RX];
+    uint32_t keep = 0;
     auto fetch = [&](int s) {  // s < s1
-        const int row = s / segs_row, w0 = (s - row * segs_row) * SEG;
-        const int b = row / g.H, h = row - b * g.H;
+        const int row = (int)fS.div((uint32_t)s), w0 = (s - row * segs_row) * SEG;
+        const int h = row - (int)g.fH.div((uint32_t)row) * g.H, pix = row * g.W + w0;
+        const int px = pix * Cs, pd = pix * Co;
+        keep = inner;
+        if (h >= 1 && h + 1 < g.H && w0 >= 1 && w0 + SEG < g.W) {
 #pragma unroll
-        for (int r = 0; r < RD; ++r) {
-            const int v = tid + NT * r;
-            if (NVD % NT == 0 || v < NVD) {
-                const int px = v / (BM / 8), cv = (v % (BM / 8)) * 8;
-                const int w = w0 + px, co = co0 + cv;
-                rd[r] = zero8();
-                if (w < g.W && co < Co) {
-                    const i64 i = (((i64)b * g.H + h) * g.W + w) * Co + co;
-                    rd[r] = masked8(ld8(dY + i), ld8(Y + i));
-                }
+            for (int r = 0; r < RX; ++r) rx[r] = ld8(Xb + (uint32_t)(px + ox[r]));
+#pragma unroll
+            for (int r = 0; r < RD; ++r) {
+                rd[r] = ld8(Db + (uint32_t)(pd + od[r]));
+                rm[r] = ld8(Yb + (uint32_t)(pd + od[r]));
             }
-        }
+        } else {
 #pragma unroll
-        for (int r = 0; r < RX; ++r) {
-            const int v = tid + NT * r;
-            if (NVX % NT == 0 || v < NVX) {
-                const int dr = v / (XW * BN / 8), rem = v - dr * (XW * BN / 8);
-                const int j = rem / (BN / 8), cv = (rem % (BN / 8)) * 8;
-                const int hh = h + dr - 1, w = w0 + j - 1, c = c0 + cv;
-                rx[r] = zero8();
-                if (hh >= 0 && hh < g.H && w >= 0 && w < g.W && c < Cp) {
-                    const i64 p = ((i64)b * g.H + hh) * g.W + w;
-                    rx[r] = c < C1 ? ld8(X1 + p * C1 + c) : ld8(X2 + p * C2 + (c - C1));
-                }
+            for (int r = 0; r < RX; ++r) {
+                const int v = tid + NT * r, dr = v / (XW * BN / 8), j = (v - dr * (XW * BN / 8)) / (BN / 8);
+                const bool ok = (unsigned)(h + dr - 1) < (unsigned)g.H && (unsigned)(w0 + j - 1) < (unsigned)g.W;
+                if (!ok) keep &= ~(1u << r);
+                rx[r] = ld8(Xb + (uint32_t)(px + (ok ? ox[r] : 0)));
+            }
+#pragma unroll
+            for (int r = 0; r < RD; ++r) {
+                const bool ok = w0 + (tid + NT * r) / (BM / 8) < g.W;
+                if (!ok) keep &= ~(0x10000u << r);
+                rd[r] = ld8(Db + (uint32_t)(pd + (ok ? od[r] : 0)));
+                rm[r] = ld8(Yb + (uint32_t)(pd + (ok ? od[r] : 0)));
             }
         }
     };
     auto stash = [&](int st) {
 #pragma unroll
-        for (int r = 0; r < RD; ++r) {
-            const int v = tid + NT * r;
-            if (NVD % NT == 0 || v < NVD) {
-                const int px = v / (BM / 8), cv = (v % (BM / 8)) * 8;
-                *reinterpret_cast<bf16x8*>(&Ds[st * DS + px * DC + cv]) = rd[r];
-            }
-        }
-#pragma unroll
         for (int r = 0; r < RX; ++r) {
             const int v = tid + NT * r;
             if (NVX % NT == 0 || v < NVX) {
                 const int dr = v / (XW * BN / 8), rem = v - dr * (XW * BN / 8);
                 const int j = rem / (BN / 8), cv = (rem % (BN / 8)) * 8;
-                *reinterpret_cast<bf16x8*>(&Xs[st * XS + (dr * XW + j) * XC + cv]) = rx[r];
+                *reinterpret_cast<bf16x8*>(&Xs[st * XS + (dr * XW + j) * XC + cv]) = keep >> r & 1u ? rx[r] : zero8();
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < RD; ++r) {
+            const int v = tid + NT * r;
+            if (NVD % NT == 0 || v < NVD) {
+                const int px = v / (BM / 8), cv = (v % (BM / 8)) * 8;
+                *reinterpret_cast<bf16x8*>(&Ds[st * DS + px * DC + cv]) =
+                    keep >> (16 + r) & 1u ? masked8(rd[r], rm[r]) : zero8();
             }
         }
     };
@@ -560,7 +608,7 @@ __global__ void __launch_bounds__(64 * W * G) k_wgrad3x3(const bf16* __restrict_
         fetch(s0 + q);
         stash(0);
     }
-    __syncthreads();
+    lds_sync();
     int st = 0;
     for (int it = 0; it < iters; ++it) {
         const int s = s0 + q + G * it;
@@ -584,44 +632,36 @@ __global__ void __launch_bounds__(64 * W * G) k_wgrad3x3(const bf16* __restrict_
                 }
             }
             if (bias && tid < BM) {
-#pragma unroll 8
+#pragma unroll
                 for (int px = 0; px < SEG; ++px) bsum += (float)D_[px * DC + tid];
             }
         }
         if (more) stash(st ^ 1);
-        __syncthreads();
+        lds_sync();
         st ^= 1;
     }
 
-    // sum the groups in LDS (group order), one tap at a time; group 0 writes
+    // sum the groups in LDS (group order), all taps of a group at a time; group 0 writes
     const i64 N1 = 9LL * Cp + 1;
     float* Pz = P + (i64)blockIdx.z * Co * N1;
-    float* red = reinterpret_cast<float*>(lds);  // [BM][BN]
+    floatx4* red = reinterpret_cast<floatx4*>(lds);  // [9][TM][TN][NT]
+    auto each = [&](auto f) {
 #pragma unroll
-    for (int t = 0; t < 9; ++t) {
-        for (int k = 1; k < G; ++k) {
-            if (q == k) {
+        for (int t = 0; t < 9; ++t)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int j = 0; j < TN; ++j)
+                for (int j = 0; j < TN; ++j) f(acc[t][i][j], red[((t * TM + i) * TN + j) * NT + tid]);
+    };
+    for (int k = 1; k < G; ++k) {
+        if (q == k) each([](floatx4& a, floatx4& r) { r = a; });
+        lds_sync();
+        if (q == 0) each([](floatx4& a, floatx4& r) { a += r; });
+        lds_sync();
+    }
+    if (q == 0) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            red[(wm + 16 * i + (lane >> 4) * 4 + e) * BN + wn + 16 * j + (lane & 15)] = acc[t][i][j][e];
-            }
-            __syncthreads();
-            if (q == 0) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            acc[t][i][j][e] += red[(wm + 16 * i + (lane >> 4) * 4 + e) * BN + wn + 16 * j + (lane & 15)];
-            }
-            __syncthreads();
-        }
-        if (q == 0) {
+        for (int t = 0; t < 9; ++t)
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -634,13 +674,13 @@ __global__ void __launch_bounds__(64 * W * G) k_wgrad3x3(const bf16* __restrict_
                         if (co < Co) Pz[(i64)co * N1 + (i64)t * Cp + c] = acc[t][i][j][e];
                     }
                 }
-        }
     }
     if (bias) {
+        float* bred = reinterpret_cast<float*>(lds);
         for (int k = 1; k < G; ++k) {
-            if (q == k && tid < BM) red[tid] = bsum;
+            if (q == k && tid < BM) bred[tid] = bsum;
             __syncthreads();
-            if (q == 0 && tid < BM) bsum += red[tid];
+            if (q == 0 && tid < BM) bsum += bred[tid];
             __syncthreads();
         }
         if (q == 0 && tid < BM && co0 + tid < Co) Pz[(i64)(co0 + tid) * N1 + 9LL * Cp] = bsum;
@@ -683,10 +723,6 @@ __device__ __forceinline__ int xcd_slot(unsigned b, unsigned G) {
     const unsigned q = G >> 3, r = G & 7u, xcd = b & 7u, loc = b >> 3;
     return (int)((xcd < r ? xcd * (q + 1) : r * (q + 1) + (xcd - r) * q) + loc);
 }
-
-// Barrier for what the threads exchange through LDS: waits for this wave's LDS
-// operations only, so that global loads issued ahead stay in flight.
-__device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 constexpr int kConvRows = 4;  // image rows of a tile
 
@@ -1475,11 +1511,13 @@ int wgrad3x3(lbm_unet* u, const Conv& c, const bf16* x1, const bf16* x2, const b
     z = (nsegs + spc - 1) / spc;  // every chunk holds at least one segment
     const dim3 grid((unsigned)((c.Co + 31) / 32), (unsigned)((c.Cp + BN - 1) / BN), (unsigned)z);
     if (wide)
-        k_wgrad3x3<2, 1, 4, 3><<<grid, 768, 0, u->stream>>>(dy, y, x1, x2, c.Cp - c.Ci2, c.Ci2, c.Co, g, segs_row,
-                                                            nsegs, spc, u->part);
+        k_wgrad3x3<2, 1, 4, 3><<<grid, 768, 0, u->stream>>>(dy, y, x1, x2, c.Cp - c.Ci2, c.Ci2, c.Co, g,
+                                                            fastdiv((uint32_t)segs_row),
+                                                            segs_row, nsegs, spc, u->part);
     else
-        k_wgrad3x3<2, 1, 2, 6><<<grid, 768, 0, u->stream>>>(dy, y, x1, x2, c.Cp - c.Ci2, c.Ci2, c.Co, g, segs_row,
-                                                            nsegs, spc, u->part);
+        k_wgrad3x3<2, 1, 2, 6><<<grid, 768, 0, u->stream>>>(dy, y, x1, x2, c.Cp - c.Ci2, c.Ci2, c.Co, g,
+                                                            fastdiv((uint32_t)segs_row),
+                                                            segs_row, nsegs, spc, u->part);
     return z;
 }
 
