@@ -34,6 +34,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "lbm.h"
@@ -212,12 +213,12 @@ struct UpGatherM {
 };
 
 // B of the transposed convolution's weight gradient: element (n = ci, k = pixel)
-// = X[pixel][ci] for n < C, 1 for n = C (the bias column)
+// = X[pixel][ci]; the bias is one more column of ones
 struct ColsOnes {
-    static constexpr bool KMAJ = false;
+    static constexpr bool KMAJ = false, ONES = true;
     const bf16* X;
     int C;
-    __device__ __forceinline__ bf16 elem(i64 n, i64 k) const { return n == C ? (bf16)1.f : X[k * C + n]; }
+    __device__ __forceinline__ bf16 elem(i64 n, i64 k) const { return X[k * C + n]; }
     struct Row {};
     __device__ __forceinline__ Row row(i64) const { return Row{}; }
     __device__ __forceinline__ bf16x8 vec(const Row&, i64 n, i64 k) const { return ld8(X + k * C + n); }
@@ -294,6 +295,12 @@ struct EpiUp {  // column n = ab * Co + co of input pixel m -> Y[out(m, ab)][co]
 
 // ---------------------------------------------------------------------------
 // The GEMM: C[M][N] = sum_k A(m, k) B(k, n) over k in [z kchunk, (z+1) kchunk)
+// in stages of KS chunks of 32.  KS = 4 where few workgroups (about 256 of the
+// transposed convolution's weight gradient) walk long reductions, 64 chunks: a
+// stage's wait for its loads is then paid 16 times instead of 64.  With that,
+// and the bias column out of the tiles (it took a column of workgroups of its
+// own), that product takes 30 us instead of 51 (mean of the three levels of 8 x
+// 256 x 256, base 32).
 // ---------------------------------------------------------------------------
 template <class L>
 __device__ __forceinline__ bf16x8 load_vec(const L& l, const typename L::Row& row, i64 mn, i64 k, i64 mnlim,
@@ -313,31 +320,44 @@ __device__ __forceinline__ bf16x8 load_vec(const L& l, const typename L::Row& ro
     }
 }
 
-// tile coordinates of vector v of a BMN x BK stage
-template <bool KMAJ, int BMN>
+// B loaders whose matrix ends in a column of ones (the last of the N columns),
+// which is no part of the tiles: its products take a constant operand
+template <class L, class = void>
+constexpr bool kOnes = false;
+template <class L>
+constexpr bool kOnes<L, std::enable_if_t<L::ONES>> = true;
+
+// tile coordinates of vector v of a BMN x SK stage
+template <bool KMAJ, int BMN, int SK>
 __device__ __forceinline__ void vec_coord(int v, int& mn, int& kk) {
     if (KMAJ) {
-        mn = v / (BK / 8);
-        kk = (v % (BK / 8)) * 8;
+        mn = v / (SK / 8);
+        kk = (v % (SK / 8)) * 8;
     } else {
         kk = v / (BMN / 8);
         mn = (v % (BMN / 8)) * 8;
     }
 }
 
-template <int BM, int BN, class LA, class LB, class EPI>
+template <int BM, int BN, int KS, class LA, class LB, class EPI>
 __global__ void __launch_bounds__(256) k_gemm(LA A, LB B, EPI epi, i64 M, i64 N, i64 K, i64 kchunk) {
-    // LDS: K-major operands as [rows][BK + 8], M/N-major as [BK][rows + 8]
-    constexpr int AC = (LA::KMAJ ? BK : BM) + 8, BC = (LB::KMAJ ? BK : BN) + 8;
-    constexpr int AR = LA::KMAJ ? BM : BK, BR = LB::KMAJ ? BN : BK;
+    // LDS: K-major operands as [rows][SK + 8], M/N-major as [SK][rows + 8]
+    constexpr int SK = BK * KS;  // K of a stage
+    constexpr int AC = (LA::KMAJ ? SK : BM) + 8, BC = (LB::KMAJ ? SK : BN) + 8;
+    constexpr int AR = LA::KMAJ ? BM : SK, BR = LB::KMAJ ? BN : SK;
     __shared__ __attribute__((aligned(16))) bf16 As[2][AR * AC];  // two stages: one barrier per K chunk
     __shared__ __attribute__((aligned(16))) bf16 Bs[2][BR * BC];
-    constexpr int NVA = BM * BK / 8, NVB = BN * BK / 8;
+    constexpr int NVA = BM * SK / 8, NVB = BN * SK / 8;
     constexpr int RA = (NVA + 255) / 256, RB = (NVB + 255) / 256;
     constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
     static_assert(TM >= 1 && TN >= 1, "tile too small");
+    constexpr bool ONES = kOnes<LB>;
+    const i64 NB = ONES ? N - 1 : N;  // the tiled columns
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // the column of ones: one more MFMA column for the first wave of each row
+    // of waves in the last column of workgroups
+    const bool ones = ONES && blockIdx.y == gridDim.y - 1 && (wave & 1) == 0;
     const i64 m0 = (i64)blockIdx.x * BM, n0 = (i64)blockIdx.y * BN;
     const i64 kb = (i64)blockIdx.z * kchunk;
     const i64 ke = kb + kchunk < K ? kb + kchunk : K;
@@ -348,6 +368,14 @@ __global__ void __launch_bounds__(256) k_gemm(LA A, LB B, EPI epi, i64 M, i64 N,
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    floatx4 acc1[ONES ? TM : 1];
+    bf16x8 one8;
+    if constexpr (ONES) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc1[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 8; ++j) one8[j] = (bf16)((lane & 15) == 0 ? 1.f : 0.f);
+    }
 
     bf16x8 ra[RA], rb[RB];
     // per-slot row state, fixed for the whole K loop
@@ -356,13 +384,13 @@ __global__ void __launch_bounds__(256) k_gemm(LA A, LB B, EPI epi, i64 M, i64 N,
 #pragma unroll
     for (int r = 0; r < RA; ++r) {
         int mn, kk;
-        vec_coord<LA::KMAJ, BM>(tid + 256 * r, mn, kk);
+        vec_coord<LA::KMAJ, BM, SK>(tid + 256 * r, mn, kk);
         rowa[r] = A.row(m0 + mn);
     }
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
         int mn, kk;
-        vec_coord<LB::KMAJ, BN>(tid + 256 * r, mn, kk);
+        vec_coord<LB::KMAJ, BN, SK>(tid + 256 * r, mn, kk);
         rowb[r] = B.row(n0 + mn);
     }
     auto fetch = [&](i64 k0) {
@@ -371,7 +399,7 @@ __global__ void __launch_bounds__(256) k_gemm(LA A, LB B, EPI epi, i64 M, i64 N,
             const int v = tid + 256 * r;
             if (NVA % 256 == 0 || v < NVA) {
                 int mn, kk;
-                vec_coord<LA::KMAJ, BM>(v, mn, kk);
+                vec_coord<LA::KMAJ, BM, SK>(v, mn, kk);
                 ra[r] = load_vec(A, rowa[r], m0 + mn, k0 + kk, M, ke);
             }
         }
@@ -380,8 +408,8 @@ __global__ void __launch_bounds__(256) k_gemm(LA A, LB B, EPI epi, i64 M, i64 N,
             const int v = tid + 256 * r;
             if (NVB % 256 == 0 || v < NVB) {
                 int mn, kk;
-                vec_coord<LB::KMAJ, BN>(v, mn, kk);
-                rb[r] = load_vec(B, rowb[r], n0 + mn, k0 + kk, N, ke);
+                vec_coord<LB::KMAJ, BN, SK>(v, mn, kk);
+                rb[r] = load_vec(B, rowb[r], n0 + mn, k0 + kk, NB, ke);
             }
         }
     };
@@ -391,7 +419,7 @@ __global__ void __launch_bounds__(256) k_gemm(LA A, LB B, EPI epi, i64 M, i64 N,
             const int v = tid + 256 * r;
             if (NVA % 256 == 0 || v < NVA) {
                 int mn, kk;
-                vec_coord<LA::KMAJ, BM>(v, mn, kk);
+                vec_coord<LA::KMAJ, BM, SK>(v, mn, kk);
                 *reinterpret_cast<bf16x8*>(&As[st][LA::KMAJ ? mn * AC + kk : kk * AC + mn]) = ra[r];
             }
         }
@@ -400,7 +428,7 @@ __global__ void __launch_bounds__(256) k_gemm(LA A, LB B, EPI epi, i64 M, i64 N,
             const int v = tid + 256 * r;
             if (NVB % 256 == 0 || v < NVB) {
                 int mn, kk;
-                vec_coord<LB::KMAJ, BN>(v, mn, kk);
+                vec_coord<LB::KMAJ, BN, SK>(v, mn, kk);
                 *reinterpret_cast<bf16x8*>(&Bs[st][LB::KMAJ ? mn * BC + kk : kk * BC + mn]) = rb[r];
             }
         }
@@ -415,37 +443,47 @@ __global__ void __launch_bounds__(256) k_gemm(LA A, LB B, EPI epi, i64 M, i64 N,
     }
     __syncthreads();
     int st = 0;
-    for (i64 k0 = kb; k0 < ke; k0 += BK) {
-        const bool more = k0 + BK < ke;
-        if (more) fetch(k0 + BK);
+    for (i64 k0 = kb; k0 < ke; k0 += SK) {
+        const bool more = k0 + SK < ke;
+        if (more) fetch(k0 + SK);
         const bf16* As_ = As[st];
         const bf16* Bs_ = Bs[st];
         // MFMA 16x16x32 operands: lane holds row (lane % 16), k = 8 (lane / 16) .. + 7
         const int kg = (lane >> 4) * 8, rl = lane & 15;
-        bf16x8 a[TM], b[TN];
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int row = wm + i * 16 + rl;
-            if constexpr (LA::KMAJ) {
-                a[i] = *reinterpret_cast<const bf16x8*>(&As_[row * AC + kg]);
-            } else {
-                a[i] = ld_tr8(&As_[wm + i * 16], AC, lane);
+        for (int ks = 0; ks < KS; ++ks) {
+            bf16x8 a[TM], b[TN];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const int row = wm + i * 16 + rl;
+                if constexpr (LA::KMAJ) {
+                    a[i] = *reinterpret_cast<const bf16x8*>(&As_[row * AC + BK * ks + kg]);
+                } else {
+                    a[i] = ld_tr8(&As_[BK * ks * AC + wm + i * 16], AC, lane);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < TN; ++i) {
+                const int row = wn + i * 16 + rl;
+                if constexpr (LB::KMAJ) {
+                    b[i] = *reinterpret_cast<const bf16x8*>(&Bs_[row * BC + BK * ks + kg]);
+                } else {
+                    b[i] = ld_tr8(&Bs_[BK * ks * BC + wn + i * 16], BC, lane);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+            if constexpr (ONES) {
+                if (ones) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+                        acc1[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], one8, acc1[i], 0, 0, 0);
+                }
             }
         }
-#pragma unroll
-        for (int i = 0; i < TN; ++i) {
-            const int row = wn + i * 16 + rl;
-            if constexpr (LB::KMAJ) {
-                b[i] = *reinterpret_cast<const bf16x8*>(&Bs_[row * BC + kg]);
-            } else {
-                b[i] = ld_tr8(&Bs_[wn + i * 16], BC, lane);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
         if (more) stash(st ^ 1);
         __syncthreads();
         st ^= 1;
@@ -456,8 +494,18 @@ __global__ void __launch_bounds__(256) k_gemm(LA A, LB B, EPI epi, i64 M, i64 N,
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                epi(m0 + wm + i * 16 + (lane >> 4) * 4 + q, n0 + wn + j * 16 + (lane & 15), acc[i][j][q]);
+            for (int q = 0; q < 4; ++q) {
+                const i64 n = n0 + wn + j * 16 + (lane & 15);
+                if (!ONES || n < NB) epi(m0 + wm + i * 16 + (lane >> 4) * 4 + q, n, acc[i][j][q]);
+            }
+    if constexpr (ONES) {
+        if (ones && (lane & 15) == 0) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) epi(m0 + wm + i * 16 + (lane >> 4) * 4 + q, NB, acc1[i][q]);
+        }
+    }
 }
 
 // Barrier for what the threads exchange through LDS: waits for this wave's LDS
@@ -936,10 +984,11 @@ inline int nchunks(i64 K, int z) {
     return (int)(n < 1 ? 1 : n);
 }
 
-template <int BM, int BN, class LA, class LB, class EPI>
+template <int BM, int BN, int KS = 1, class LA, class LB, class EPI>
 void launch_gemm(hipStream_t s, const LA& A, const LB& B, const EPI& e, i64 M, i64 N, i64 K, int z) {
-    dim3 grid((unsigned)((M + BM - 1) / BM), (unsigned)((N + BN - 1) / BN), (unsigned)nchunks(K, z));
-    k_gemm<BM, BN, LA, LB, EPI><<<grid, 256, 0, s>>>(A, B, e, M, N, K, kchunk_of(K, z));
+    const i64 NB = kOnes<LB> ? N - 1 : N;
+    dim3 grid((unsigned)((M + BM - 1) / BM), (unsigned)((NB + BN - 1) / BN), (unsigned)nchunks(K, z));
+    k_gemm<BM, BN, KS, LA, LB, EPI><<<grid, 256, 0, s>>>(A, B, e, M, N, K, kchunk_of(K, z));
 }
 
 // A GEMM without split-K: 128-row tiles when they give at least 1024
@@ -1563,7 +1612,7 @@ void up_bwd(lbm_unet* u, const Up& p, const bf16* x, const bf16* dy, bf16* dx, i
     ColsOnes B2{x, p.Ci};
     const int z = splits_for(4LL * p.Co, N1, P, u->part_n);
     EpiPartial e2{u->part, 4LL * p.Co, N1};
-    launch_gemm<64, 64>(u->stream, A2, B2, e2, 4LL * p.Co, N1, P, z);
+    launch_gemm<64, 64, 4>(u->stream, A2, B2, e2, 4LL * p.Co, N1, P, z);
     const int nz = nchunks(P, z);
     if (nz >= 32)
         k_reduce_up<16><<<reduce_blocks(4LL * p.Co * N1, 16), 256, 0, u->stream>>>(u->part, nz, p.Co, p.Ci,
