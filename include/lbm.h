@@ -133,9 +133,12 @@ typedef struct {
     int step_kernel;      /* LBM_STEP_AUTO (default): D3Q19 lattices (either wall scheme; not the phase-field
                              model) with nx a multiple of 64 (at most 1024), ny a multiple of 4 and nz even
                              take one pass over the populations per step (the
-                             collision also sums the next step's density); LBM_STEP_SPLIT: a density pass,
-                             then the collision.  Both compute the same step; the density sums differ in
-                             order, so the fields agree to rounding. */
+                             collision also sums the next step's density); D2Q9 lattices and 2-D batches
+                             run a step in one launch from their second step on (steps issued while the
+                             stream is being captured take the split step); LBM_STEP_SPLIT: a density
+                             pass, then the collision.  All compute the same step; the one-pass step's
+                             density sums differ in order, so there the fields agree to rounding, and the
+                             D2Q9 launch gives the split step's bits. */
     double pf_A, pf_kappa;  /* phase-field model: free-energy coefficients (default 0.01, 0.02) */
     double pf_gamma;        /* mobility coefficient: M = pf_gamma (pf_tau - 1/2) (default 1) */
     double pf_tau;          /* relaxation time of the order-parameter populations, > 1/2 (default 1) */
@@ -340,7 +343,8 @@ lbm_status lbm_young_series(lbm_ctx* ctx, lbm_young* out, int cap, int* n_writte
 /* Step the lattice nsteps times (no measurement) with a HIP event pair
  * around every kernel launch, and report the mean duration in milliseconds of
  * each kernel kind: names[i] (static strings) and ms[i] for i < *n_kinds
- * (cap entries at most).  Synchronises. */
+ * (cap entries at most).  A D2Q9 lattice is stepped by the split step's
+ * kernels here.  Synchronises. */
 lbm_status lbm_profile_step(lbm_ctx* ctx, int64_t nsteps, const char** names, double* ms,
                             int cap, int* n_kinds);
 
@@ -383,9 +387,10 @@ lbm_status lbm_measure_field(int lattice, int precision, const int n[3], const v
  * Each case has its own lattice size, one solid primitive (wettability as in
  * lbm_solid) and one drop (Eq. 16, W = 10); all cases share the fluid, the
  * collision and the boundary settings of the base configuration.  Cases are
- * packed in one allocation; every phase of a step is one persistent launch
- * over a work list of (case, tile) items, and step loops are captured in a
- * hipGraph.  A case advanced in a batch equals the same case advanced alone
+ * packed in one allocation.  A 2-D step is one launch over the tiles of all
+ * cases, a 3-D step one persistent launch per phase over a work list of
+ * (case, tile) items (in 2-D the split step of LBM_STEP_SPLIT), and step loops
+ * are captured in a hipGraph.  A case advanced in a batch equals the same case advanced alone
  * with lbm_step, bit for bit.  The contact angle of every case is measured in
  * the step (2 sides in 2-D, 16 sectors in 3-D).
  *
@@ -465,8 +470,8 @@ lbm_status lbm_batch_get_info(lbm_batch* b, lbm_batch_info* info);
 lbm_status lbm_batch_tune(lbm_batch* b, const char* cache_path);
 /* Advance every case nsteps steps (no measurement) with a HIP event pair
  * around each launch of kb_density, kb_mu and kb_collide (kb_pf_density,
- * kb_pf_mu and kb_pf_collide for the phase-field model), and report their
- * mean duration in milliseconds: names[i] (static strings) and ms[i] for
+ * kb_pf_mu and kb_pf_collide for the phase-field model; the split step's
+ * kernels, in 2-D too), and report their mean duration in milliseconds: names[i] (static strings) and ms[i] for
  * i < *n_kinds (cap entries at most).  Synchronises.  Errors: LBM_E_ARG,
  * LBM_E_STATE before any initial state, LBM_E_DEVICE, LBM_E_NONFINITE. */
 lbm_status lbm_batch_profile_step(lbm_batch* b, int64_t nsteps, const char** names, double* ms, int cap,
