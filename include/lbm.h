@@ -135,7 +135,8 @@ typedef struct {
                              take one pass over the populations per step (the
                              collision also sums the next step's density); D2Q9 lattices and 2-D batches
                              run a step in one launch from their second step on (steps issued while the
-                             stream is being captured take the split step); LBM_STEP_SPLIT: a density
+                             stream is being captured take the split step, and so do all later steps of
+                             that lattice, whose step counter the replays move); LBM_STEP_SPLIT: a density
                              pass, then the collision.  All compute the same step; the one-pass step's
                              density sums differ in order, so there the fields agree to rounding, and the
                              D2Q9 launch gives the split step's bits. */

@@ -128,6 +128,10 @@ struct lbm_ctx {
     hipGraphExec_t graph2d[2] = {nullptr, nullptr};
     Tile2d* tiles = nullptr;
     int ntiles = 0, shape2d = 0;
+    // a captured lbm_step has been recorded: its replays move the device's step
+    // counter (ctl->t) and not t, so only the device knows which steps measure
+    // and from which one the body force acts; kept for the life of the context
+    bool replayed = false;
     // phase-field model: the order-parameter populations (same form and
     // buffer parity as f) and the order parameter, whose solid layers hold phi_w
     bool pf = false;
@@ -1485,12 +1489,14 @@ lbm_status lbm_step(lbm_ctx* c, int64_t nsteps, int measure_every, lbm_angle* se
     // windows of them as a captured graph, from buffer 0), the measurement's
     // launches only on measure steps, which the host knows.  A state S_t is
     // first brought to pull form by a split step.  A stream under capture
-    // takes the split step, whose launches decide on the device what they do.
-    bool one2d = c->one2d;
+    // takes the split step, whose launches decide on the device what they do,
+    // and so do all later calls: replays advance the device's counter alone.
+    bool one2d = c->one2d && !c->replayed;
     if (one2d) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
             (void)hipGetLastError();
+            c->replayed = cs == hipStreamCaptureStatusActive;
             one2d = false;
         }
     }
