@@ -154,11 +154,15 @@ __device__ __forceinline__ void collide_bgk9(const R S[L2::Q], double rd, C Fx, 
     }
 }
 
+// field and wall are one array in the phase-field model (phi of the fluid nodes
+// and of the solid layers): a workgroup reads it at solid nodes only and stores,
+// on measure steps, at fluid nodes only, so that no entry is both.  (Reading it
+// at every node, its value unused at fluid ones, raced with those stores.)
 template <typename R, typename C, bool MRT, int MODEL, int TW, int TH, int NT, int WPE>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) k_step2d(const Tile2d* __restrict__ tiles, long long N,
                                                const R* __restrict__ fin, R* __restrict__ fout,
-                                               const R* __restrict__ gin, R* __restrict__ gout, R* __restrict__ field,
-                                               const R* __restrict__ wall, const uint8_t* __restrict__ cls, WallBC bc,
+                                               const R* __restrict__ gin, R* __restrict__ gout, R* field,
+                                               const R* wall, const uint8_t* __restrict__ cls, WallBC bc,
                                                Thermo th, Collision<C> cp, PhaseField pf, DevCtl* __restrict__ ctl,
                                                MeasureSlots* __restrict__ slots, double rho_m, R inv_b, int meas,
                                                int tick, int grav) {
@@ -230,11 +234,13 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) 
             if (SOLID) {
                 c = at(cls, ix);
                 m = at(bc.nbmask, ix);
-                wv = at(wall, ix);
+                if constexpr (MODEL != M2_PHASE) wv = at(wall, ix);
             }
             R Q[L2::Q];
             pull2d<R, SOLID, EDGE>(src, N, t, ix, x, y, m, Q);
             const bool fluid = (c & CLS_MASK) == CLS_FLUID;
+            if constexpr (SOLID && MODEL == M2_PHASE)
+                if (!fluid) wv = at(wall, ix);
             if constexpr (SOLID && MODEL != M2_PHASE) {
                 if (bc.bouzidi && (c & CLS_CURVED)) {
                     Dims d;
