@@ -344,8 +344,9 @@ lbm_status lbm_young_series(lbm_ctx* ctx, lbm_young* out, int cap, int* n_writte
 /* Step the lattice nsteps times (no measurement) with a HIP event pair
  * around every kernel launch, and report the mean duration in milliseconds of
  * each kernel kind: names[i] (static strings) and ms[i] for i < *n_kinds
- * (cap entries at most).  A D2Q9 lattice is stepped by the split step's
- * kernels here.  Synchronises. */
+ * (cap entries at most).  The kernels are those lbm_step runs; from an initial
+ * or written state a D2Q9 lattice takes the split step's for all nsteps, after
+ * a step of it k_step2d.  Synchronises. */
 lbm_status lbm_profile_step(lbm_ctx* ctx, int64_t nsteps, const char** names, double* ms,
                             int cap, int* n_kinds);
 
@@ -410,7 +411,9 @@ typedef struct {
 } lbm_case;
 
 typedef struct {
-    int autotune;        /* 1: time candidate tile widths / workgroups per CU and keep the fastest */
+    int autotune;        /* 1: time candidate tile widths / workgroups per CU and keep the fastest (a 2-D step in
+                            one launch takes neither: only its time is taken, and tiles of 64 nodes with 4
+                            workgroups per CU serve the measurement) */
     int tile_w;          /* 64, 128 or 256 nodes per tile row (tile = 256 nodes) when not tuning */
     int blocks_per_cu;   /* persistent workgroups per compute unit when not tuning (1..32) */
     const char* cache_path; /* JSON file of tuned choices keyed by the case table, or NULL */
@@ -420,7 +423,7 @@ typedef struct {
     int64_t total_nodes, fluid_nodes;  /* lattice nodes of all cases (each row is padded to a multiple of
                                           64 nodes in device memory), fluid nodes among them */
     int32_t ncases, tile_w, blocks_per_cu, n_items;
-    double tune_ms_per_step;  /* time per step of the chosen launch shape (0 if not tuned) */
+    double tune_ms_per_step;  /* time per step of the chosen launch shape, or of the 2-D step (0 if not tuned) */
     int64_t step;
     double rho_g, rho_l;
 } lbm_batch_info;
@@ -471,9 +474,11 @@ lbm_status lbm_batch_get_info(lbm_batch* b, lbm_batch_info* info);
 lbm_status lbm_batch_tune(lbm_batch* b, const char* cache_path);
 /* Advance every case nsteps steps (no measurement) with a HIP event pair
  * around each launch of kb_density, kb_mu and kb_collide (kb_pf_density,
- * kb_pf_mu and kb_pf_collide for the phase-field model; the split step's
- * kernels, in 2-D too), and report their mean duration in milliseconds: names[i] (static strings) and ms[i] for
- * i < *n_kinds (cap entries at most).  Synchronises.  Errors: LBM_E_ARG,
+ * kb_pf_mu and kb_pf_collide for the phase-field model), or of k_step2d where
+ * 2-D cases take it (not from an initial or written state, where the split
+ * step's kernels run for all nsteps), and report their mean duration in
+ * milliseconds: names[i] (static strings) and ms[i] for i < *n_kinds (cap entries
+ * at most).  Synchronises.  Errors: LBM_E_ARG,
  * LBM_E_STATE before any initial state, LBM_E_DEVICE, LBM_E_NONFINITE. */
 lbm_status lbm_batch_profile_step(lbm_batch* b, int64_t nsteps, const char** names, double* ms, int cap,
                                   int* n_kinds);

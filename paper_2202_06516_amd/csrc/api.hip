@@ -1726,9 +1726,9 @@ lbm_status lbm_get_info(lbm_ctx* c, lbm_info* info) {
 }
 
 lbm_status lbm_profile_step(lbm_ctx* c, int64_t nsteps, const char** names, double* ms, int cap, int* n_kinds) {
-    static const char* kNames[11] = {"k_density", "k_fill_layer1", "k_fill_layer2", "k_mu",    "k_collide",
+    static const char* kNames[12] = {"k_density", "k_fill_layer1", "k_fill_layer2", "k_mu",    "k_collide",
                                      "k_cross",   "k_finalize",    "k_step",        "k_ghost", "k_force",
-                                     "k_interp_wall"};
+                                     "k_interp_wall", "k_step2d"};
     if (!c || !names || !ms || !n_kinds) return LBM_E_ARG;
     if (!c->have_state) return fail(c, LBM_E_STATE, "profile: no state");
     if (nsteps < 1) return fail(c, LBM_E_ARG, "profile: nsteps >= 1");
@@ -1740,14 +1740,22 @@ lbm_status lbm_profile_step(lbm_ctx* c, int64_t nsteps, const char** names, doub
     if (c->fused && !c->rho_valid) dispatch<OpDerive>(c, true);
     hipEvent_t ev[24];
     for (auto& e : ev) HIPCHK(c, hipEventCreate(&e));
-    double tot[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    int cnt[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    double tot[12] = {};
+    int cnt[12] = {};
+    // the kernels lbm_step would run: a 2-D lattice's single launch, unless it starts from a state S_t
+    const bool one2d = c->one2d && !c->replayed && c->fstar;
     for (int64_t t = 0; t < nsteps; ++t) {
         int kinds[12];
         if (c->fused) {
             dispatch<OpFusedStep>(c, c->cur, c->fstar, c->rcur, &mp, ev, kinds);
             c->rcur ^= 1;
             c->rho = c->rhob[c->rcur];
+        } else if (one2d) {
+            HIPCHK(c, hipEventRecord(ev[0], c->stream));
+            dispatch<OpOne2d>(c, c->cur, &mp, false, c->t >= c->cfg.g_start_step);
+            HIPCHK(c, hipEventRecord(ev[1], c->stream));
+            kinds[0] = 11;
+            kinds[1] = -1;
         } else {
             dispatch<OpStep>(c, c->cur, c->fstar, &mp, ev, kinds);
         }
@@ -1764,7 +1772,7 @@ lbm_status lbm_profile_step(lbm_ctx* c, int64_t nsteps, const char** names, doub
     }
     for (auto& e : ev) (void)hipEventDestroy(e);
     int n = 0;
-    for (int k = 0; k < 11 && n < cap; ++k) {
+    for (int k = 0; k < 12 && n < cap; ++k) {
         if (!cnt[k]) continue;
         names[n] = kNames[k];
         ms[n] = tot[k] / cnt[k];

@@ -598,7 +598,8 @@ class Batch:
         self._check(lib().lbm_batch_tune(self._h, cache_path.encode() if cache_path else None))
 
     def profile(self, nsteps):
-        """Mean ms per launch of kb_density, kb_mu and kb_collide over nsteps eager steps."""
+        """Mean ms per launch of the step's kernels over nsteps eager steps: k_step2d for 2-D cases that have
+        stepped, else kb_density, kb_mu and kb_collide."""
         names = (C.c_char_p * 8)()
         ms = (C.c_double * 8)()
         n = C.c_int()
