@@ -33,10 +33,12 @@ COUNTED_TRAFFIC = {("k_step", 256, "f32", "bgk", "chemical-potential"): 13015528
                    ("k_step", 256, "f32", "mrt", "chemical-potential"): 12774044 * 128 + 1700 * 64 + 21594828 * 64,
                    ("k_collide", 256, "f32", "bgk", "phase-field"):
                        24626936 * 128 + 2257 * 64 + 36426673 * 64 + 439204 * 32}
-# the same for kb_collide of the batched solver on the seeded table, from FETCH_SIZE x 2 and WRITE_SIZE in KiB
-# (the scaling of a plain copy; profiles/kb_collide_batch_d2q9_512cases.md), keyed by (number of cases,
-# precision, force model)
-BATCH_COUNTED_TRAFFIC = {(512, "f32", "chemical-potential"): (1392231 * 2 + 1386829) * 1024}
+# the same for the batched solver's k_step2d on the seeded table (profiles/k_step2d_d2q9.md), its writes that are
+# not 64-byte requests counted as 32 bytes; keyed by (kernel, number of cases, precision, force model)
+BATCH_COUNTED_TRAFFIC = {("k_step2d", 512, "f32", "chemical-potential"):
+                         14052079 * 128 + 31939 * 64 + 21880697 * 64 + 1063387 * 32,
+                         ("k_step2d", 512, "f32", "phase-field"):
+                         38366115 * 128 + 30901 * 64 + 65355968 * 64 + 2687390 * 32}
 
 
 def parse():
@@ -252,12 +254,13 @@ def batch_bench(args):
     b.sync()
     ang = b.angles()
     valid = sum(1 for a in ang if a.status == 0)
-    # dominant kernel: kb_collide, timed with HIP events on the batch's stream over eager steps
+    # dominant kernel: the step's single launch k_step2d (or kb_collide of the split step), timed with HIP events
+    # on the batch's stream over eager steps
     prof = b.profile(args.profile_steps)
     Q, P = 9, (8 if args.precision == "f64" else 4)
     # algorithmic: each population read once and written once (both sets of the phase-field model)
     coll_bytes = inf["fluid_nodes"] * 2 * Q * P * (2 if pf else 1)
-    kern = "kb_pf_collide" if pf else "kb_collide"
+    kern = "k_step2d" if "k_step2d" in prof else "kb_pf_collide" if pf else "kb_collide"
     coll_ms = prof[kern]
     achieved = coll_bytes / (coll_ms * 1e-3) / 1e9
     what = ("R_s U[16,128], r0 U[12,96], mu_w U[-0.01,0.1], Tr=0.8, MRT tau=1, angle every 100" if not pf else
@@ -276,7 +279,7 @@ def batch_bench(args):
         "cases_with_contact_angle": valid,
         "roofline": {"bound": "hbm", "kernel": kern, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": BATCH_COUNTED_TRAFFIC.get((args.cases, args.precision, args.model)),
+                     "traffic": BATCH_COUNTED_TRAFFIC.get((kern, args.cases, args.precision, args.model)),
                      "bytes_per_launch": coll_bytes, "mean_ms": round(coll_ms, 5)},
         "kernels_ms": {k: round(v, 5) for k, v in prof.items()},
     }
