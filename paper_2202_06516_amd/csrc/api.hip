@@ -580,12 +580,14 @@ struct Run {
         // Workgroup = one row of nx threads; the launch bound follows it.  In
         // double the bound of 1024 threads (128 registers) spills up to 340
         // bytes a lane, bounds of 384 and 512 (up to 206 registers) nothing: at
-        // 384 x 320 x 256, ms per launch before and after, F64 MRT 7.2 and 2.7,
+        // 384 x 320 x 256, ms per launch at 1024 and 384, F64 MRT 7.2 and 2.7,
         // BGK 6.4 and 2.7, mixed MRT 5.3 and 1.8, BGK 2.1 and 1.35; at 512 x
-        // 256 x 128 F64 MRT 3.5 and 1.26, mixed 2.5 and 0.75.  In float nothing
-        // spills at 1024 and smaller bounds give nothing (512 x 256 x 128: 0.612
-        // at 1024, 0.620 at 512), except where they carry the stencil ring
-        // (BGK, six waves a row).
+        // 256 x 128, at 1024 and 512, F64 MRT 3.5 and 1.26, mixed 2.5 and 0.75.
+        // Rows of up to 384 nodes run within 1% at either of the two, but for
+        // F64 MRT at 320 (us per step at 512 and 384: 320 x 128 x 128 501 and
+        // 494, 320 x 256 x 128 994 and 976).  In float nothing spills at 1024,
+        // and smaller bounds pay where they let the stencil ring in (FP32 BGK,
+        // rows of 321 to 448 nodes; figures at RING).
 #define LBM_K_STEP(NX)                                                                                          \
     k_step<R, C, PULL, MRT, SC, kFusedTY, NX><<<grd, blk, 0, c->stream>>>(                                       \
         fin, fout, rho, (const R*)c->mu, (const R*)c->force, rnext, (R*)c->gy, (R*)c->gz, (R*)c->gyz, c->cls, c->d, \
@@ -597,6 +599,7 @@ struct Run {
             else LBM_K_STEP(1024);
         } else if constexpr (!MRT && !SC) {
             if (c->d.nx > 320 && c->d.nx <= 384) LBM_K_STEP(384);
+            else if (c->d.nx > 384 && c->d.nx <= 448) LBM_K_STEP(512);
             else LBM_K_STEP(1024);
         }
         else LBM_K_STEP(1024);

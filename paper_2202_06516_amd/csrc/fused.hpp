@@ -239,12 +239,21 @@ __global__ void __launch_bounds__(NX) k_step(const R* __restrict__ fin, R* __res
     // written two planes before another thread reads it and overwritten two
     // planes after, with a barrier at the end of every plane in between.
     // FP32 storage and rows of up to 256 nodes (32 KB); with FP32 BGK also rows
-    // of 321 to 384 (48 KB, the NX = 384 kernel).  Measured there, without and
-    // with the ring, ms per launch: 384 x 320 x 256 BGK 1.35 and 1.25, MRT 1.41
-    // and 1.43; 384 x 256 x 128 BGK 0.458 and 0.463, MRT 0.485 and 0.577; rows
-    // of 320 BGK 0.387 and 0.430, MRT 0.42 and 0.56.  (Rows of 512 with the
-    // ring ran no faster at 512^3.)
-    constexpr bool RING = !SC && sizeof(R) == 4 && (NX <= 256 || (NX == 384 && !MRT && sizeof(C) == 4));
+    // of 321 to 448 (48 and 64 KB, the NX = 384 and 512 kernels).  Measured
+    // without and with the ring, FP32 BGK, us per step:
+    //   384 x 64 x 64 140 and 133, 128 x 128 277 and 275, 192 x 160 566 and 502,
+    //     256 x 128 516 and 510, 256 x 256 1190 and 1060, 320 x 256 1471 and
+    //     1364, 384 x 192 1237 and 1233, 512 x 128 1183 and 1060, 384 x 384 2499
+    //     and 2326: none slower
+    //   448 x 64 x 64 147 and 140, 128 x 128 322 and 317, 256 x 128 600 and 586,
+    //     320 x 256 1685 and 1631, 384 x 192 1622 and 1596: none slower
+    //   320 x 128 x 128 240 and 252, 256 x 128 438 and 461, 384 x 192 1040 and
+    //     1114, but 256 x 256 995 and 916: off
+    //   512 x 64 x 64 159 and 153, 256 x 256 1392 and 1356, but 192 x 160 664 and
+    //     667, 512 x 512 5490 and 5450 to 5640: off
+    // FP32 MRT, ms per launch: 384 x 320 x 256 1.41 and 1.43, 384 x 256 x 128
+    // 0.485 and 0.577, rows of 320 0.42 and 0.56: off.
+    constexpr bool RING = !SC && sizeof(R) == 4 && (NX <= 256 || ((NX == 384 || NX == 512) && !MRT && sizeof(C) == 4));
     __shared__ R ring[RING ? 4 : 1][TY][2][RING ? NX : 1];
 #pragma unroll
     for (int k = 0; k < TY + 2; ++k) acc[k][0][x] = acc[k][1][x] = acc[k][2][x] = C(0);
