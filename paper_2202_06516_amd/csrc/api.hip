@@ -1030,16 +1030,28 @@ lbm_status lbm_create(const lbm_config* cfg, lbm_ctx** out) {
         // 0.574, 0.584, 0.570 ms and the ghost sums 0.025, 0.022, 0.020 ms;
         // without the ring 64 planes (one workgroup per CU) took 0.729 ms, and
         // at 512^3 16 and 32 planes 4.61 and 4.59 ms
-        // Rows of 257 to 384 nodes (two workgroups of five or six waves per CU:
-        // 512 at a time) start at 16: the 640 workgroups of 32 planes at 384 x
-        // 320 x 256 run in two rounds, the second a quarter full (the walk over
-        // 8, 16, 32 planes: FP32 MRT 1.37, 1.41, 1.48 ms, BGK 1.30, 1.25, 1.39,
-        // F64 MRT 2.77, 2.71, 2.97; at 320 x 320 x 256 MRT 1.17, 1.09, 1.28).
+        // Rows of 257 to 384 nodes (five or six waves) take 16 planes where that
+        // fills the device's rounds of 256 workgroups better: the 640 workgroups
+        // of 32 planes at 384 x 320 x 256 are 2.5 rounds that last three, the
+        // 1280 of 16 five.  us per step, 32 and 16 planes, at 384 nodes FP32 BGK
+        // / FP32 MRT / F64 BGK: 576 workgroups of 32 planes 1415 and 1240 / 1522
+        // and 1305 / 2851 and 2581, 640: 1503 and 1378 / 1605 and 1557 / 3273 and
+        // 3067, 896: 1952 and 1819 / 2428 and 2095 / 4055 and 3839, 1152: 2511
+        // and 2332 / 2624 and 2615 / 5091 and 4927.  Where 32 planes fill their
+        // rounds they stay ahead, above all at 320 nodes (FP32 MRT 512
+        // workgroups 930 and 1105, 768: 1485 and 1607, 1280: 2374 and 2524; at
+        // 384 nodes 1097 and 1270, 1643 and 1797; FP32 BGK and F64 0 to 14%),
+        // but for FP32 at 1024 (320 nodes 2058 and 1919, 384 MRT 2549 and 2356)
+        // and 384 MRT at 1280 (3231 and 3069).
         const char* e = std::getenv("LBM_FUSED_ZC");
-        int zc = e ? std::atoi(e) : (c->d.nx > 256 && c->d.nx <= 384 ? 16 : 32);
+        int zc = e ? std::atoi(e) : 32;
         while (zc > 2 && c->d.nz % zc) zc >>= 1;
-        if (!e)
-            while (zc > 8 && (long long)(c->d.ny / kFusedTY) * (c->d.nz / zc) < 512) zc >>= 1;
+        if (!e) {
+            const long long columns = c->d.ny / kFusedTY;
+            auto rounds = [&](int planes) { return (columns * (c->d.nz / planes) + 255) / 256; };
+            if (c->d.nx > 256 && c->d.nx <= 384 && zc == 32 && rounds(16) < 2 * rounds(32)) zc = 16;
+            while (zc > 8 && columns * (c->d.nz / zc) < 512) zc >>= 1;
+        }
         c->fzc = zc;
         // (its node indices and the byte offsets of its population accesses, up to
         // five arrays from one base, are 32-bit)
