@@ -587,7 +587,8 @@ struct Run {
         // F64 MRT at 320 (us per step at 512 and 384: 320 x 128 x 128 501 and
         // 494, 320 x 256 x 128 994 and 976).  In float nothing spills at 1024,
         // and smaller bounds pay where they let the stencil ring in (FP32 BGK,
-        // rows of 321 to 448 nodes; figures at RING).
+        // rows of 321 to 448 nodes, unless there are 257 to 511 workgroups; figures
+        // at RING).
 #define LBM_K_STEP(NX)                                                                                          \
     k_step<R, C, PULL, MRT, SC, kFusedTY, NX><<<grd, blk, 0, c->stream>>>(                                       \
         fin, fout, rho, (const R*)c->mu, (const R*)c->force, rnext, (R*)c->gy, (R*)c->gz, (R*)c->gyz, c->cls, c->d, \
@@ -598,8 +599,10 @@ struct Run {
             else if (c->d.nx <= 512) LBM_K_STEP(512);
             else LBM_K_STEP(1024);
         } else if constexpr (!MRT && !SC) {
-            if (c->d.nx > 320 && c->d.nx <= 384) LBM_K_STEP(384);
-            else if (c->d.nx > 384 && c->d.nx <= 448) LBM_K_STEP(512);
+            // (257 to 511 workgroups: some CUs hold two and set the pace, and two share a CU better without the ring)
+            const bool ring = c->d.nx > 320 && c->d.nx <= 448 && (grd.x <= 256 || grd.x >= 512);
+            if (ring && c->d.nx <= 384) LBM_K_STEP(384);
+            else if (ring) LBM_K_STEP(512);
             else LBM_K_STEP(1024);
         }
         else LBM_K_STEP(1024);

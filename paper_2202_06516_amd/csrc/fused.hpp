@@ -241,12 +241,15 @@ __global__ void __launch_bounds__(NX) k_step(const R* __restrict__ fin, R* __res
     // FP32 storage and rows of up to 256 nodes (32 KB); with FP32 BGK also rows
     // of 321 to 448 (48 and 64 KB, the NX = 384 and 512 kernels).  Measured
     // without and with the ring, FP32 BGK, us per step:
-    //   384 x 64 x 64 140 and 133, 128 x 128 277 and 275, 192 x 160 566 and 502,
+    //   384 x 64 x 64 140 and 133, 32 x 192 146 and 138, 192 x 160 566 and 502,
     //     256 x 128 516 and 510, 256 x 256 1190 and 1060, 320 x 256 1471 and
-    //     1364, 384 x 192 1237 and 1233, 512 x 128 1183 and 1060, 384 x 384 2499
-    //     and 2326: none slower
-    //   448 x 64 x 64 147 and 140, 128 x 128 322 and 317, 256 x 128 600 and 586,
-    //     320 x 256 1685 and 1631, 384 x 192 1622 and 1596: none slower
+    //     1364, 384 x 192 1237 and 1233, 384 x 384 2499 and 2326; of 46 lattices
+    //     the ones with 257 to 511 workgroups are slower (96 x 96, 288: 225 and
+    //     244; 64 x 192, 384: 251 and 259), with 512 to 768 of 8 planes they are
+    //     within 2% (256 x 64 274 and 278, 128 x 128 279 and 276)
+    //   448 x 64 x 64 147 and 140, 128 x 128 321 and 314, 256 x 128 600 and 586,
+    //     320 x 256 1685 and 1631, 384 x 192 1622 and 1596; 96 x 96, 288
+    //     workgroups: 250 and 260
     //   320 x 128 x 128 240 and 252, 256 x 128 438 and 461, 384 x 192 1040 and
     //     1114, but 256 x 256 995 and 916: off
     //   512 x 64 x 64 159 and 153, 256 x 256 1392 and 1356, but 192 x 160 664 and
