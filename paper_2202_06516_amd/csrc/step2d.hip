@@ -535,16 +535,27 @@ std::vector<Tile2d> tiles2d(const Dims* dims, int n, int shape) {
     return v;
 }
 
-// One launch of a small lattice lasts as long as one workgroup does: 16 x 16
+// One launch of a small lattice lasts as long as one workgroup does, and 16 x 16
 // tiles with a thread for every node of the halo as well (one gather per
-// thread) take 6.1 us per step at 256^2 in FP32 (7.3 us in FP64) against 9.7
-// (13.0) for 64 x 16 ones, and stay ahead up to two workgroups per compute
-// unit (at 340^2 7.0 against 9.9 us, at 440^2 10.0 each).  Beyond, the halo
-// counts: 64 x 16 tiles gather 1.7 times the populations, 16 x 16 ones 3.1
-// times (1000^2: 27.9 against 51.7 us).  With FP64 arithmetic 32 x 16 tiles of
-// 512 threads are ahead from about 400,000 nodes (720^2: 27.9 against 33.2
-// us, 1400^2: 74.3 against 83.2), except in the phase-field model, whose second
-// population set fills the registers.
+// thread) are the shorter chain: chemical potential, MRT, us per step at 256^2
+// 6.5 against 10.2 with 64 x 16 ones in FP32 (7.7 against 13.5 in FP64).  They
+// fill the device with two workgroups per compute unit (512 tiles, 131,000
+// nodes); beyond, the halo counts: near a solid 16 x 16 tiles gather 3.1 times
+// the populations that they collide and 64 x 16 ones 2.1 times (elsewhere 2.25
+// and 1.7; pseudopotential 1.27 and 1.16, phase field 1.56 and 1.33).  us per
+// step of 16 x 16 and 64 x 16 tiles, MRT FP32 and FP64:
+//            chemical potential       pseudopotential         phase field
+//   340^2    7.8 10.3   12.2 14.0     4.7 5.4    6.4  6.8     6.4  8.2   10.6 11.2
+//   380^2    9.3 10.4   13.1 16.0     6.2 5.4    7.5  6.6     8.4  9.0   15.4 12.0
+//   420^2   10.6 10.5   16.6 14.6     6.5 5.3    8.5  7.4    11.8 10.2   17.6 13.8
+//   460^2   11.0 10.4   19.1 15.0     7.0 5.6   11.1  7.8    14.7 11.6   21.6 14.1
+// so they cross between 340^2 and 420^2 for every model; one line, at the last
+// size where all of these are ahead, serves them all (with BGK the phase field
+// in FP64 alone is behind there, 12.5 against 10.7).  With double arithmetic
+// 32 x 16 tiles of 512 threads are ahead of 64 x 16 ones from about 400,000
+// nodes (chemical potential FP64, 720^2: 27.9 against 33.2 us, 1400^2: 74.3
+// against 83.2), except in the phase-field model, whose second population set
+// fills the registers.
 int shape2d_for(long long nodes, int precision, int model) {
     if (nodes <= 116000) return 0;
     return precision != LBM_F32 && nodes >= 400000 && model != M2_PHASE ? 2 : 1;

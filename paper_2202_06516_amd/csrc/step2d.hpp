@@ -23,12 +23,15 @@
 //
 // Bound: on small lattices the chain of a launch, one class and population
 // load, the LDS passes and the stores (6 us per step at 256^2 FP32 instead of
-// 22 us of dependent launches); on large ones vector instructions (about 600
-// per node with the halo's share, two thirds of the issue slots), then memory
-// (72 bytes per node).  Measured against the split step, per step: 128^2 FP64
-// 14 instead of 30 us with the reads of a 20-step call, 3000 x 400 FP32 33
-// instead of 51 us, ten 700 x 400 cases 67 instead of 97 us, 256 uneven cases
-// (20 M nodes) 0.52 instead of 0.78 ms.
+// 22 us of dependent launches); on large ones vector instructions (560 per
+// node of 3000 x 400 in FP32 with the halo's share, 0.74 per busy cycle of a
+// compute unit, which issues one at most; 512 cases 713 and 0.86), then memory
+// (72 bytes per node, 1.16 times that counted).  The phase field is bound by
+// memory (5.4 TB/s counted over 512 cases; in FP32 its MRT collision spills 24
+// registers, a part of that traffic).  Measured against the split step, per
+// step: 128^2 FP64 14 instead of 30 us with the reads of a 20-step call, 3000 x
+// 400 FP32 33 instead of 51 us, ten 700 x 400 cases 67 instead of 97 us, 256
+// uneven cases (20 M nodes) 0.52 instead of 0.78 ms.
 #pragma once
 
 #include <vector>
@@ -59,7 +62,7 @@ struct Shape2d {
 // One launch of the step over a tile list.
 struct Step2dArgs {
     int precision;             // LBM_F32 / LBM_F64 / LBM_F32_MIXED
-    int model, mrt, shape;     // M2_*, 1: MRT, index into shapes2d
+    int model, mrt, shape;     // M2_*, 1: MRT, index of shape2d()
     const Tile2d* tiles;
     int ntiles;
     long long N;               // population stride
